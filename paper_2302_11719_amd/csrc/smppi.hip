@@ -646,6 +646,27 @@ extern "C" smppi_status smppi_execute_curvilinear(smppi_ctx ctx, const smppi_bat
 }
 
 // ------------------------------------------------------------------ weights
+// Threads and register slots from the largest problem: 256 threads hold up to
+// 1024 samples (fewer waves to meet in the reductions), 1024 threads up to
+// 4096, 16384 or, in FP32, 65536 (64 values and their temporaries just fit the
+// 128 registers of a 1024-thread workgroup; 64 doubles do not).
+template <class R>
+static void launch_weights(const smppi_batch* b, const R* S, double lambda, R* w, R* stats, hipStream_t s) {
+  const dim3 grid(b->n_problems);
+  const R il = (R)(1.0 / lambda);
+  if (b->k_max <= 1024)
+    hipLaunchKernelGGL((k_weights<R, 256, 4, true>), grid, dim3(256), 0, s, b->k_off, S, il, w, stats);
+  else if (b->k_max <= 4096)
+    hipLaunchKernelGGL((k_weights<R, 1024, 4, true>), grid, dim3(1024), 0, s, b->k_off, S, il, w, stats);
+  else if (b->k_max <= 16384)
+    hipLaunchKernelGGL((k_weights<R, 1024, 16, true>), grid, dim3(1024), 0, s, b->k_off, S, il, w, stats);
+  else if (b->k_max <= 65536 && sizeof(R) == 4)
+    hipLaunchKernelGGL((k_weights<R, 1024, (sizeof(R) == 4 ? 64 : 16), true>), grid, dim3(1024), 0, s, b->k_off, S,
+                       il, w, stats);
+  else
+    hipLaunchKernelGGL((k_weights<R, 1024, 16, false>), grid, dim3(1024), 0, s, b->k_off, S, il, w, stats);
+}
+
 extern "C" smppi_status smppi_weights(smppi_ctx ctx, const smppi_batch* batch, const void* S, double lambda, void* w,
                                       void* stats, void* stream) {
   if (!ctx) return SMPPI_ERR_INVALID_ARGUMENT;
@@ -656,13 +677,11 @@ extern "C" smppi_status smppi_weights(smppi_ctx ctx, const smppi_batch* batch, c
   (void)hipSetDevice(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (batch->dtype == SMPPI_F32)
-    hipLaunchKernelGGL((k_weights<float>), dim3(batch->n_problems), dim3(256), 0, s, batch->k_off,
-                       static_cast<const float*>(S), (float)(1.0 / lambda), static_cast<float*>(w),
-                       static_cast<float*>(stats));
+    launch_weights<float>(batch, static_cast<const float*>(S), lambda, static_cast<float*>(w),
+                          static_cast<float*>(stats), s);
   else
-    hipLaunchKernelGGL((k_weights<double>), dim3(batch->n_problems), dim3(256), 0, s, batch->k_off,
-                       static_cast<const double*>(S), 1.0 / lambda, static_cast<double*>(w),
-                       static_cast<double*>(stats));
+    launch_weights<double>(batch, static_cast<const double*>(S), lambda, static_cast<double*>(w),
+                           static_cast<double*>(stats), s);
   return check_launch(ctx, "k_weights");
 }
 
