@@ -15,6 +15,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "curv8.hpp"
+#include "pipe.hpp"
 
 using namespace smppi;
 
@@ -358,6 +359,25 @@ static smppi_status launch_rollout(smppi_ctx ctx, const smppi_batch* b, const Ro
   const size_t lds = stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, a.p.obs_max);
   RolloutArgs<R> ra = a;
   ra.obs_pad = nullptr;
+  if constexpr (NOBS == 0) {
+    // Few samples: the step pipeline (same bits).  16 samples per workgroup up to
+    // two workgroups per compute unit (K = 4096, T = 50: FP32 50.7 -> 22.8 us, FP64
+    // 127 -> 31.7; at 16384 it takes 30.3 / 79.6 against 23.9 / 58.2 with 64); 64
+    // samples up to four per unit in FP32 and two in FP64 (K = 65536, T = 100, FP32:
+    // 98.9 -> 77.7 us; at 131072, T = 50: 76.4 against 63.6 with one wave per 64
+    // samples, FP64 at 65536: 165.9 against 128.7).
+    const int64_t n16 = (int64_t)b->n_problems * ((b->k_max + 15) / 16);
+    const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
+    const size_t l16 = lds + sizeof(typename RolloutPipe<R, 16>::Lds), l64 = lds + sizeof(typename RolloutPipe<R, 64>::Lds);
+    if (n16 <= 2 * ctx->n_cu && l16 <= (size_t)ctx->max_lds) {
+      hipLaunchKernelGGL((k_rollout_pipe<R, 16>), dim3((b->k_max + 15) / 16, b->n_problems), dim3(RP_BLK), l16, s, ra);
+      return check_launch(ctx, "k_rollout_pipe");
+    }
+    if (n64 <= (sizeof(R) == 4 ? 4 : 2) * ctx->n_cu && l64 <= (size_t)ctx->max_lds) {
+      hipLaunchKernelGGL((k_rollout_pipe<R, 64>), dim3((b->k_max + 63) / 64, b->n_problems), dim3(RP_BLK), l64, s, ra);
+      return check_launch(ctx, "k_rollout_pipe");
+    }
+  }
   if (NOBS > 0 && sizeof(R) == 4) {
     // FP32 obstacles are evaluated per wave from padded slots in the scratch buffer
     smppi_status st = need_scratch(ctx, sizeof(float4) * (size_t)b->n_problems * NOBS, 0, "smppi_rollout");
