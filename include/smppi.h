@@ -199,7 +199,8 @@ int smppi_abi_version(void);
 /* Size the ctx's scratch for the plain calls on any batch within the host
  * bounds of `batch` (n_problems, k_max, t_max, dtype; its device arrays are not
  * read): the update's and the adjoint's per-workgroup partials
- * (dtype bytes x B x ceil(k_max / workgroup samples) x 2 x t_max), the padded
+ * (dtype bytes x B x ceil(k_max / workgroup samples) x 2 x t_max), the adjoint's
+ * stored states or checkpoints (see smppi_rollout_backward), the padded
  * obstacle slots of FP32 rollouts (B x 64 x 16 bytes) and B ticket counters.
  * Allocates (and synchronises) only when the ctx holds less; the scratch never
  * shrinks.  Call it before smppi_rollout (FP32 with obstacles), smppi_update
@@ -288,10 +289,13 @@ smppi_status smppi_update(smppi_ctx ctx, const smppi_batch* batch, const smppi_m
                           const uint32_t* iter, void* V_plus, void* stream);
 
 /* Adjoint rollout: grad_V = sum_m grad_S[m] dL_m/dV for the objective above,
- * where sample m's trajectory uses the same noise as smppi_rollout.  States are
- * recomputed from per-sample checkpoints (every min(ceil(sqrt(t_max)), 12)
- * steps, in the ctx scratch, with each step's window segment) instead of being
- * stored.  Every 64 samples write a partial; a second small kernel adds them in a fixed order
+ * where sample m's trajectory uses the same noise as smppi_rollout.  The forward
+ * pass stores every state, unclipped control and window segment in the ctx scratch
+ * when that takes at most 1 GiB (B x ceil(k_max / 64) x 64 x (t_max + 1) x
+ * (8 dtype bytes + 4)); otherwise states are recomputed from per-sample
+ * checkpoints (every min(ceil(sqrt(t_max)), 12) steps, with each step's window
+ * segment).  Groups of 64 samples without upstream gradient are skipped.  Every 64
+ * samples write a partial; a second small kernel adds them in a fixed order
  * (the result does not depend on scheduling).  grad_V has the
  * layout of V (dtype).  Gradients pass through the clip where it is inactive and
  * through the hinge where it is active (one-sided at ties). */
@@ -303,7 +307,8 @@ smppi_status smppi_rollout_backward(smppi_ctx ctx, const smppi_batch* batch, con
 
 /* smppi_rollout_backward for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): same arguments, same kernels and results, but the ticket
+ * hipMalloc): same arguments, the same results up to rounding (bit for bit
+ * where both entry points store every state), but the ticket
  * counters and per-workgroup partials live in a fixed scratch array that each
  * GPU holds for the life of the process (looked up at smppi_create), so no
  * smppi_reserve_batch is needed and nothing is allocated.  Limits: at most 4096
@@ -311,7 +316,8 @@ smppi_status smppi_rollout_backward(smppi_ctx ctx, const smppi_batch* batch, con
  * slice sums, per-lane checkpoints and window indices (about B x n x (2 t_max x
  * dtype bytes + 64 x (ceil(t_max / s) x (8 dtype bytes + 4) + 4 t_max)) bytes,
  * n = ceil(k_max / 64), s = min(ceil(sqrt(t_max)), 12); K = 65536 at T = 100
- * needs about 51 MB), else SMPPI_ERR_SHAPE before anything is enqueued.  Every call on a
+ * needs about 51 MB), else SMPPI_ERR_SHAPE before anything is enqueued; every
+ * state is stored instead of checkpoints where that fits the 64 MiB too.  Every call on a
  * GPU shares that GPU's array (the counters are cleared by a kernel at the
  * start of each call): calls that overlap on one GPU, from any ctx or thread,
  * race and must be ordered by the caller. */

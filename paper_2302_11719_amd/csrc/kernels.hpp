@@ -646,7 +646,8 @@ __global__ __launch_bounds__(UPD_BLOCK) void k_update(UpdateArgs<R> a) {
 }
 
 // ============================================================== adjoint
-// Per-lane reverse sweep with checkpoints every `seg_len` steps (global scratch
+// The adjoint of batches whose states would not fit the scratch (k_backward_pipe
+// takes the others): per-lane reverse sweep with checkpoints every `seg_len` steps (global scratch
 // of the workgroup: written once, read once per segment) and the states of one
 // segment recomputed into LDS (layout [slot][component][lane]).  Keeping only
 // the segment in LDS leaves room for enough workgroups per CU that the large

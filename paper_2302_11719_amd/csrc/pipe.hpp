@@ -39,7 +39,7 @@ struct RolloutPipe {
   static constexpr int NCTL = 6;                 // delta, sin/m, cos/m, cos l_f/I_z, a tau, control cost
   struct Lds {
     R ctl[D][NCTL][NS];
-    R stg[NS == 64 ? 1 : D][NS][12];  // NS = 16: velocities of the four RK4 stages (v_x, v_y, omega)
+    R stg[NS == 64 ? 1 : D][NS == 64 ? 1 : NS][12];  // NS = 16: velocities of the four RK4 stages (v_x, v_y, omega)
     R pos[D][3][NS];                  // p_x, p_y, v_x of x_{t+1}
     int cnt[8];                       // steps: [0] noise, [1] velocity, [2] pose (NS = 64: RK4) written; [4], [5] read
   };

@@ -16,6 +16,7 @@
 #include "kernels.hpp"
 #include "curv8.hpp"
 #include "pipe.hpp"
+#include "adjoint_pipe.hpp"
 
 using namespace smppi;
 
@@ -64,7 +65,7 @@ smppi_status smppi::ensure_tickets(smppi_ctx ctx, int n) {
 // The adjoint's scratch for a batch: per-workgroup partials [B][nblk][2][t_max],
 // slice sums [B][ceil(nblk / SUM_SLICE)][2][t_max] (dtype) and ticket counters
 // [B][ceil(2 t_max / 64)] for the sum kernel.
-AdjScratch smppi::adjoint_scratch(const smppi_batch* b) {
+AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
   AdjScratch a;
   a.r = b->dtype == SMPPI_F32 ? sizeof(float) : sizeof(double);
   a.nblk = std::max(1, (std::max(0, b->k_max) + WAVE - 1) / WAVE);
@@ -81,6 +82,11 @@ AdjScratch smppi::adjoint_scratch(const smppi_batch* b) {
   a.ck_bytes = (size_t)b->n_problems * a.nblk *
                (a.r == sizeof(float) ? adj_ck_bytes_per_wg<float>(b->t_max, seg, 8, true)
                                      : adj_ck_bytes_per_wg<double>(b->t_max, seg, 8, true));
+  // every state instead of checkpoints where that takes little enough memory
+  a.rows_bytes = (size_t)b->n_problems * a.nblk *
+                 (a.r == sizeof(float) ? adj_rows_bytes_per_wg<float>(b->t_max) : adj_rows_bytes_per_wg<double>(b->t_max));
+  a.stored = a.rows_bytes <= max_rows;
+  if (a.stored) a.ck_bytes = std::max(a.ck_bytes, a.rows_bytes);
   // padded obstacle slots of the FP32 adjoint ([B][64] float4), after the checkpoints
   a.pad_off = (a.ck_off + a.ck_bytes + 255) & ~(size_t)255;
   a.pad_bytes = b->dtype == SMPPI_F32 ? sizeof(float4) * (size_t)b->n_problems * kMaxObs : 0;
@@ -745,7 +751,15 @@ extern "C" smppi_status smppi_update(smppi_ctx ctx, const smppi_batch* batch, co
 
 // ------------------------------------------------------------------ adjoint
 template <class R, int NOBS>
-static smppi_status launch_backward(smppi_ctx ctx, const smppi_batch* b, const BackwardArgs<R>& a, hipStream_t s) {
+static smppi_status launch_backward(smppi_ctx ctx, const smppi_batch* b, const BackwardArgs<R>& a, bool stored,
+                                    hipStream_t s) {
+  const size_t lds_p =
+      stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, adj_pipe_obs<R>(a.p.obs_max)) + sizeof(AdjPipeLds<R>);
+  if (stored && lds_p <= (size_t)ctx->max_lds) {
+    const BackwardPipeArgs<R> pa{a, a.ck};
+    hipLaunchKernelGGL((k_backward_pipe<R, NOBS>), dim3(a.nblk_max, b->n_problems), dim3(RP_BLK), lds_p, s, pa);
+    return check_launch(ctx, "k_backward_pipe");
+  }
   const size_t lds = stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, a.p.obs_max) + adj_lds_bytes<R>(a.p.t_max, a.seg_len);
   if (lds > (size_t)ctx->max_lds)
     return fail(ctx, SMPPI_ERR_SHAPE, "adjoint needs %zu B of LDS per workgroup (device max %d)", lds, ctx->max_lds);
@@ -759,8 +773,7 @@ template <class R>
 static smppi_status backward_launch(smppi_ctx ctx, const smppi_batch* b, const smppi_model* m, const smppi_cost* c,
                                     const smppi_noise* n, const smppi_track* t, const void* x0, const void* V,
                                     const uint32_t* iter, const void* gS, const smppi_objective* ob, void* gV,
-                                    void* scratch, uint32_t* tickets, hipStream_t s) {
-  const AdjScratch as = adjoint_scratch(b);
+                                    const AdjScratch& as, void* scratch, uint32_t* tickets, hipStream_t s) {
   BackwardArgs<R> a;
   a.p = problem_args<R>(ctx, b, t, n, x0, iter);
   a.M = dev_model<R>(m);
@@ -784,7 +797,8 @@ static smppi_status backward_launch(smppi_ctx ctx, const smppi_batch* b, const s
     if ((st = check_launch(ctx, "k_pad_obs"))) return st;
     a.obs_pad = pad;
   }
-  st = t->obs_max > 0 ? launch_backward<R, kMaxObs>(ctx, b, a, s) : launch_backward<R, 0>(ctx, b, a, s);
+  st = t->obs_max > 0 ? launch_backward<R, kMaxObs>(ctx, b, a, as.stored, s)
+                      : launch_backward<R, 0>(ctx, b, a, as.stored, s);
   if (st) return st;
   return launch_sum_partials<R>(ctx, b, as, scratch, tickets, gV, s);
 }
@@ -798,7 +812,7 @@ static smppi_status backward_t(smppi_ctx ctx, const smppi_batch* b, const smppi_
   const AdjScratch as = adjoint_scratch(b);
   if ((st = need_scratch(ctx, as.pad_off + as.pad_bytes, (int)as.tickets, "smppi_rollout_backward")))
     return st;
-  return backward_launch<R>(ctx, b, m, c, n, t, x0, V, iter, gS, ob, gV, ctx->scratch, ctx->tickets, s);
+  return backward_launch<R>(ctx, b, m, c, n, t, x0, V, iter, gS, ob, gV, as, ctx->scratch, ctx->tickets, s);
 }
 
 smppi_status smppi::validate_objective(smppi_ctx ctx, const smppi_objective* o) {
@@ -890,7 +904,9 @@ extern "C" smppi_status smppi_rollout_backward_noalloc(smppi_ctx ctx, const smpp
   if ((st = validate_backward(ctx, batch, model, cost, noise, track, x0, V, iter, grad_S, objective, grad_V)))
     return st;
   if (!ctx->noalloc) return fail(ctx, SMPPI_ERR_UNSUPPORTED, "no fixed scratch on device %d", ctx->device);
-  const AdjScratch as = adjoint_scratch(batch);
+  // every state where that fits the fixed array too, else checkpoints
+  AdjScratch as = adjoint_scratch(batch);
+  if (as.pad_off + as.pad_bytes > kNoAllocBytes - kNoAllocTicketBytes) as = adjoint_scratch(batch, 0);
   const size_t part = as.pad_off + as.pad_bytes;
   if (as.tickets * sizeof(uint32_t) > kNoAllocTicketBytes || part > kNoAllocBytes - kNoAllocTicketBytes)
     return fail(ctx, SMPPI_ERR_SHAPE,
@@ -908,10 +924,10 @@ extern "C" smppi_status smppi_rollout_backward_noalloc(smppi_ctx ctx, const smpp
   if ((st = check_launch(ctx, "k_zero_u32"))) return st;
   void* pp = base + kNoAllocTicketBytes;
   if (batch->dtype == SMPPI_F32)
-    return backward_launch<float>(ctx, batch, model, cost, noise, track, x0, V, iter, grad_S, objective, grad_V, pp,
-                                  tickets, s);
-  return backward_launch<double>(ctx, batch, model, cost, noise, track, x0, V, iter, grad_S, objective, grad_V, pp,
-                                 tickets, s);
+    return backward_launch<float>(ctx, batch, model, cost, noise, track, x0, V, iter, grad_S, objective, grad_V, as,
+                                  pp, tickets, s);
+  return backward_launch<double>(ctx, batch, model, cost, noise, track, x0, V, iter, grad_S, objective, grad_V, as,
+                                 pp, tickets, s);
 }
 
 // ------------------------------------------------------------------ repair
