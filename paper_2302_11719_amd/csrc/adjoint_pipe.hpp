@@ -33,20 +33,15 @@ namespace smppi {
 
 // Stored rows of a workgroup: p_x, p_y, psi, v_x, v_y, omega of x_t and the two
 // unclipped controls of step t, [t_max + 1][8][64], then the window segment of
-// x_t, [t_max + 1][64].
-constexpr int ADJ_ROW = 8;
+// x_t, [t_max + 1][64] (curvilinear model: eight states and two controls).
+constexpr int ADJ_ROW = 8, ADJ_ROW8 = 10;
 template <class R>
 __host__ __device__ inline size_t adj_rows_bytes_per_wg(int t_max) {
-  return (size_t)(t_max + 1) * WAVE * (ADJ_ROW * sizeof(R) + sizeof(int));
+  return (size_t)(t_max + 1) * WAVE * ADJ_ROW8 * sizeof(R);
 }
 
 constexpr int REV_D = 2;   // ring slots of the stage rows
 constexpr int REV_DS = 4;  // ring slots of the small rows
-
-template <class R>
-struct alignas(4 * sizeof(R)) Quad {
-  R v[4];
-};
 
 template <class R>
 struct RevLds {
@@ -173,7 +168,7 @@ struct RevBarrier {
 
 // Clip, control cost and the sum over the samples of step i (t = T - 1 - i), once
 // wave 2 has written its control gradient.
-template <class R>
+template <class R, int ROW>
 struct RevSum {
   struct In { R r0, r1; };
   const R* rows;
@@ -183,11 +178,11 @@ struct RevSum {
   R g, c0, c1, lo0, hi0, lo1, hi1;
   In cur, n1;
   __device__ __forceinline__ In load(int t) const {
-    const R* r = rows + (size_t)max(t, 0) * ADJ_ROW * WAVE;
-    return In{r[6 * WAVE], r[7 * WAVE]};
+    const R* r = rows + ((size_t)max(t, 0) * ROW + ROW - 2) * WAVE;
+    return In{r[0], r[WAVE]};
   }
-  __device__ __forceinline__ RevSum(const BackwardArgs<R>& a, const R* rows_, const R* Vs_, R* gp_, int T_, int lane_,
-                                    R g_, const DevModel<R>& M, const DevCost<R>& C, const DevObjective<R>& ob)
+  __device__ __forceinline__ RevSum(const R* rows_, const R* Vs_, R* gp_, int T_, int lane_, R g_,
+                                    const DevModel<R>& M, const DevCost<R>& C, const DevObjective<R>& ob)
       : rows(rows_), Vs(Vs_), gp(gp_), T(T_), lane(lane_), seen(0), g(g_) {
     c0 = ob.w_S * C.ctrl_w[0];
     c1 = ob.w_S * C.ctrl_w[1];
@@ -196,15 +191,16 @@ struct RevSum {
     cur = load(T - 1);
     n1 = load(T - 2);
   }
-  __device__ __forceinline__ void step(RevLds<R>& P, int i, uint32_t* err) {
+  // ring: [REV_DS][2][64]; cnt[2] steps written, cnt[5] read
+  __device__ __forceinline__ void step(const R (*ring)[2][WAVE], int* cnt, int i, uint32_t* err) {
     const int t = T - 1 - i;
     const In n2 = load(t - 2);
     const R v0 = Vs[t], v1 = Vs[T + t];
     const R u0 = clamp_r(cur.r0, lo0, hi0), u1 = clamp_r(cur.r1, lo1, hi1);
     const bool pass0 = cur.r0 >= lo0 && cur.r0 <= hi0, pass1 = cur.r1 >= lo1 && cur.r1 <= hi1;
-    wave_wait(&P.cnt[2], i, seen, err);
-    const R gd = P.gd[i % REV_DS][0][lane], gt = P.gd[i % REV_DS][1][lane];
-    wave_publish(&P.cnt[5], i + 1);
+    wave_wait(cnt + 2, i, seen, err);
+    const R gd = ring[i % REV_DS][0][lane], gt = ring[i % REV_DS][1][lane];
+    wave_publish(cnt + 5, i + 1);
     const R gv0 = (pass0 ? fma_r(c0, v0, gd) : R(0)) + c0 * u0;
     const R gv1 = (pass1 ? fma_r(c1, v1, gt) : R(0)) + c1 * u1;
     // a sample with zero upstream contributes exactly zero, even when it diverged
@@ -260,11 +256,13 @@ __global__ __launch_bounds__(RP_BLK) void k_backward_pipe(BackwardPipeArgs<R> ba
   int* segs = reinterpret_cast<int*>(wg + (size_t)(a.p.t_max + 1) * ADJ_ROW * WAVE * sizeof(R));
   // ---- forward: every state, unclipped control and window segment
   if (w == 0) {
-    pipe_noise<R, 64>(M, C, Vs, T, a.p.seed, (uint32_t)m, (uint32_t)(a.p.pid_base + b), a.p.iter[b], a.p.nominal != 0,
-                      L.fwd, a.p.err, [&](int t, R r0, R r1, R, R) {
-                        rows[((size_t)t * ADJ_ROW + 6) * WAVE] = r0;
-                        rows[((size_t)t * ADJ_ROW + 7) * WAVE] = r1;
-                      });
+    pipe_noise<R, 64, RolloutPipe<R, 64>::D, 2>(
+        M, C, Vs, T, a.p.seed, (uint32_t)m, (uint32_t)(a.p.pid_base + b), a.p.iter[b], a.p.nominal != 0, L.fwd.cnt,
+        a.p.err, [&](int t, int s, R v0, R v1, R r0, R r1, R u0, R u1) {
+          pipe_put_ctl<R, 64>(L.fwd, M, C, t, s, v0, v1, u0, u1);
+          rows[((size_t)t * ADJ_ROW + 6) * WAVE] = r0;
+          rows[((size_t)t * ADJ_ROW + 7) * WAVE] = r1;
+        });
   } else if (w == 1) {
     auto put = [&](int t, const State<R>& x) {
       R* o = rows + (size_t)(t + 1) * ADJ_ROW * WAVE;
@@ -365,7 +363,7 @@ __global__ __launch_bounds__(RP_BLK) void k_backward_pipe(BackwardPipeArgs<R> ba
     auto load = [&](int t) { return In{row(t, 2)}; };
     In cur = load(T - 1), n1 = load(T - 2);
     RevBarrier<R, 0> bar(a, tr, rows, segs, b, T, lane, C, ob);
-    RevSum<R> sum(a, rows, Vs, gp, T, lane, g, M, C, ob);
+    RevSum<R, ADJ_ROW> sum(rows, Vs, gp, T, lane, g, M, C, ob);
     R lx = C.phi_w * bar.qe * bar.gnx, ly = C.phi_w * bar.qe * bar.gny, lp = R(0);
     int seen = 0, seenb = 0;
     for (int i = 0; i < T; ++i) {
@@ -407,9 +405,9 @@ __global__ __launch_bounds__(RP_BLK) void k_backward_pipe(BackwardPipeArgs<R> ba
       ly += db.v[3];
       cur = n1;
       n1 = n2;
-      if (NOBS > 0 && i >= 1) sum.step(P, i - 1, a.p.err);
+      if (NOBS > 0 && i >= 1) sum.step(P.gd, P.cnt, i - 1, a.p.err);
     }
-    if (NOBS > 0) sum.step(P, T - 1, a.p.err);
+    if (NOBS > 0) sum.step(P.gd, P.cnt, T - 1, a.p.err);
   } else if (w == 2) {
     // cotangent of (v_x, v_y, omega) and the control gradient
     const R sv = ob.w_S * R(2) * C.q_v;
@@ -462,8 +460,8 @@ __global__ __launch_bounds__(RP_BLK) void k_backward_pipe(BackwardPipeArgs<R> ba
         wave_publish(&P.cnt[3], i + 1);
       }
     } else {
-      RevSum<R> sum(a, rows, Vs, gp, T, lane, g, M, C, ob);
-      for (int i = 0; i < T; ++i) sum.step(P, i, a.p.err);
+      RevSum<R, ADJ_ROW> sum(rows, Vs, gp, T, lane, g, M, C, ob);
+      for (int i = 0; i < T; ++i) sum.step(P.gd, P.cnt, i, a.p.err);
     }
   }
 }

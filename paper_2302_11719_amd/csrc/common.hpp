@@ -54,7 +54,7 @@ struct AdjScratch {
   int n_problems;
 };
 // Most memory the adjoint takes to store every state of every sample in the ctx
-// scratch (K = 65536, T = 100 in FP32: 238 MB); larger batches use checkpoints.
+// scratch (K = 65536, T = 100 in FP32: 265 MB); larger batches use checkpoints.
 constexpr size_t kMaxRows = (size_t)1 << 30;
 AdjScratch adjoint_scratch(const smppi_batch* b, size_t max_rows = kMaxRows);
 size_t batch_scratch_bytes(const smppi_batch* b);

@@ -72,10 +72,11 @@ __device__ __forceinline__ R kappa_cell(const CurvView<R>& cv, R s, R& slope) {
 }
 
 // Body part of f: (v_x, v_y, r, omega_F, omega_R) from themselves and the control
-// (the tyre forces depend on neither the path coordinates nor the curvature).
+// (the tyre forces depend on neither the path coordinates nor the curvature);
+// fxf: the front longitudinal force on request.
 template <class R>
 __device__ __forceinline__ void deriv_c8_body(const DevModel<R>& M, const DevWheels<R>& Wh, const Ctl8<R>& c,
-                                              const C8<R>& x, C8<R>& d) {
+                                              const C8<R>& x, C8<R>& d, R* fxf = nullptr) {
   const R vt = fmax(x.vx, M.v_min);
   const R inv = rcp_r(vt);
   const R a = fma_r(M.lf, x.r, x.vy);
@@ -84,6 +85,7 @@ __device__ __forceinline__ void deriv_c8_body(const DevModel<R>& M, const DevWhe
   const R vwF = fma_r(x.vx, c.cd, a * c.sd);
   const R FxF = Wh.C_x * (fma_r(Wh.r_w, x.wF, -vwF) * inv);
   const R FxR = Wh.C_x * (fma_r(Wh.r_w, x.wR, -x.vx) * inv);
+  if (fxf) *fxf = FxF;
   d.vx = fma_r(FxR + fma_r(FxF, c.cd, -(FyF * c.sd)), M.inv_m, fma_r(-M.c_v, x.vx, x.vy * x.r));
   d.vy = fma_r(FyR + fma_r(FxF, c.sd, FyF * c.cd), M.inv_m, -(x.vx * x.r));
   d.r = fma_r(M.lf_Iz, fma_r(FxF, c.sd, FyF * c.cd), -(M.lr_Iz * FyR));
@@ -509,7 +511,8 @@ struct C8BackwardArgs {
   int seg_len;
 };
 
-// grad_V = sum_m grad_S[m] dL_m/dV: one 64-lane workgroup per 64 samples, grid
+// The adjoint of batches whose states would not fit the scratch (k_backward_c8_pipe
+// takes the others).  grad_V = sum_m grad_S[m] dL_m/dV: one 64-lane workgroup per 64 samples, grid
 // (nblk_max, B); each workgroup writes its partial (k_sum_partials adds them).
 template <class R>
 __global__ __launch_bounds__(WAVE) void k_backward_c8(C8BackwardArgs<R> g) {

@@ -33,8 +33,7 @@ constexpr int RP_BLK = 4 * WAVE;
 template <class R, int NS>
 struct RolloutPipe {
   static constexpr int LN = WAVE / NS;           // noise lanes per sample
-  static constexpr int PASS = 2 * LN;            // steps per pass of the noise wave
-  static constexpr int D = NS == 64 ? 8 : 16;    // ring slots (a power of two, >= 2 * PASS)
+  static constexpr int D = NS == 64 ? 8 : 16;    // ring slots
   static constexpr int LT = NS == 64 ? 2 : 4;    // lanes per sample of the offset/cost waves
   static constexpr int NCTL = 6;                 // delta, sin/m, cos/m, cos l_f/I_z, a tau, control cost
   struct Lds {
@@ -43,6 +42,11 @@ struct RolloutPipe {
     R pos[D][3][NS];                  // p_x, p_y, v_x of x_{t+1}
     int cnt[8];                       // steps: [0] noise, [1] velocity, [2] pose (NS = 64: RK4) written; [4], [5] read
   };
+};
+
+template <class R>
+struct alignas(4 * sizeof(R)) Quad {
+  R v[4];
 };
 
 // Lane q of a quad (or pair) to all its lanes' neighbours, by DPP.
@@ -147,23 +151,25 @@ __device__ __forceinline__ R window4_lanes(const TrackView<R>& tr, const WindowR
   return bd;
 }
 
-// The noise wave.  put(t, r0, r1, u0, u1): called by the lane that owns step t
-// of its sample, before the step is published.
-template <class R, int NS, class Put>
+// The noise wave: 64 / NS lanes per sample, rings of D slots, cnt[0] the steps
+// written, cnt[4] (and, ROOM = 2, cnt[5]) the steps that have left the pipeline.
+// put(t, s, v0, v1, r0, r1, u0, u1): the lane that owns step t of sample s
+// writes its rows (controls v, with noise r, clipped u) before they are published.
+template <class R, int NS, int D, int ROOM, class Put>
 __device__ void pipe_noise(const DevModel<R>& M, const DevCost<R>& C, const R* Vs, int T, uint32_t seed, uint32_t m,
-                           uint32_t pid, uint32_t it, bool nominal, typename RolloutPipe<R, NS>::Lds& P, uint32_t* err,
-                           Put put) {
-  using RP = RolloutPipe<R, NS>;
-  const int lane = threadIdx.x % WAVE, s = lane / RP::LN, l = lane % RP::LN;
+                           uint32_t pid, uint32_t it, bool nominal, int* cnt, uint32_t* err, Put put) {
+  constexpr int LN = WAVE / NS, PASS = 2 * LN;
+  static_assert(D >= 2 * PASS && (D & (D - 1)) == 0, "ring too short");
+  const int lane = threadIdx.x % WAVE, s = lane / LN, l = lane % LN;
   int seen0 = 0, seen1 = 0;
-  for (int tp = 0; tp < T; tp += RP::PASS) {
+  for (int tp = 0; tp < T; tp += PASS) {
     const int t0 = tp + 2 * l;
     R z[4] = {R(0), R(0), R(0), R(0)};
     if (!nominal) normals4<R>(seed, (uint32_t)(t0 >> 1), m, pid, it, z);
-    if (tp >= RP::D) {  // room: the pass's last step reuses the slot of step tp + PASS - 1 - D
-      const int last = min(tp + RP::PASS, T) - 1 - RP::D;
-      wave_wait(&P.cnt[4], last, seen0, err);
-      if (NS == 64) wave_wait(&P.cnt[5], last, seen1, err);
+    const int last = min(tp + PASS, T) - 1 - D;  // the pass's last step reuses this step's slot
+    if (last >= 0) {
+      wave_wait(cnt + 4, last, seen0, err);
+      if (ROOM == 2) wave_wait(cnt + 5, last, seen1, err);
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -174,21 +180,29 @@ __device__ void pipe_noise(const DevModel<R>& M, const DevCost<R>& C, const R* V
         R e0 = C.sigma[0] * z[2 * k], e1 = C.sigma[1] * z[2 * k + 1];
         asm volatile("" : "+v"(e0), "+v"(e1));
         const R r0 = v0 + e0, r1 = v1 + e1;
-        const R u0 = clamp_r(r0, M.u_lo[0], M.u_hi[0]);
-        const R u1 = clamp_r(r1, M.u_lo[1], M.u_hi[1]);
-        const StepCtl<R> c = step_ctl(M, u0, u1);
-        R(*o)[NS] = P.ctl[t % RP::D];
-        o[0][s] = c.delta;
-        o[1][s] = c.sd_m;
-        o[2][s] = c.cd_m;
-        o[3][s] = c.lfcd_Iz;
-        o[4][s] = c.a_tau;
-        o[5][s] = fma_r(C.ctrl_w[0] * v0, u0, C.ctrl_w[1] * v1 * u1);
-        put(t, r0, r1, u0 - v0, u1 - v1);
+        put(t, s, v0, v1, r0, r1, clamp_r(r0, M.u_lo[0], M.u_hi[0]), clamp_r(r1, M.u_lo[1], M.u_hi[1]));
       }
     }
-    wave_publish(&P.cnt[0], min(tp + RP::PASS, T));
+    wave_publish(cnt, min(tp + PASS, T));
   }
+}
+// Control cost of a step, lambda_u v^T Sigma^-1 u.
+template <class R>
+__device__ __forceinline__ R pipe_ctl_cost(const DevCost<R>& C, R v0, R v1, R u0, R u1) {
+  return fma_r(C.ctrl_w[0] * v0, u0, C.ctrl_w[1] * v1 * u1);
+}
+// Ring row of a step (six-state model).
+template <class R, int NS>
+__device__ __forceinline__ void pipe_put_ctl(typename RolloutPipe<R, NS>::Lds& P, const DevModel<R>& M,
+                                             const DevCost<R>& C, int t, int s, R v0, R v1, R u0, R u1) {
+  const StepCtl<R> c = step_ctl(M, u0, u1);
+  R(*o)[NS] = P.ctl[t % RolloutPipe<R, NS>::D];
+  o[0][s] = c.delta;
+  o[1][s] = c.sd_m;
+  o[2][s] = c.cd_m;
+  o[3][s] = c.lfcd_Iz;
+  o[4][s] = c.a_tau;
+  o[5][s] = pipe_ctl_cost(C, v0, v1, u0, u1);
 }
 
 template <class R, int NS>
@@ -313,13 +327,15 @@ __global__ __launch_bounds__(RP_BLK) void k_rollout_pipe(RolloutArgs<R> a) {
   if (w == 0) {
     const int m = m_base + lane / RP::LN;
     R* eo = (a.eps_out && m < d.K) ? a.eps_out + (size_t)(d.k0 + m) * a.p.t_max * 2 : nullptr;
-    pipe_noise<R, NS>(M, C, Vs, T, a.p.seed, (uint32_t)m, (uint32_t)(a.p.pid_base + b), a.p.iter[b],
-                      a.p.nominal != 0, P, a.p.err, [&](int t, R, R, R e0, R e1) {
-                        if (eo) {
-                          eo[2 * t] = e0;
-                          eo[2 * t + 1] = e1;
-                        }
-                      });
+    pipe_noise<R, NS, RP::D, NS == 64 ? 2 : 1>(
+        M, C, Vs, T, a.p.seed, (uint32_t)m, (uint32_t)(a.p.pid_base + b), a.p.iter[b], a.p.nominal != 0, P.cnt, a.p.err,
+        [&](int t, int s, R v0, R v1, R, R, R u0, R u1) {
+          pipe_put_ctl<R, NS>(P, M, C, t, s, v0, v1, u0, u1);
+          if (eo) {
+            eo[2 * t] = u0 - v0;
+            eo[2 * t + 1] = u1 - v1;
+          }
+        });
   } else if (NS == 64 && w == 1) {
     if constexpr (NS == 64) pipe_rk4<R>(M, x0, T, P, a.p.err, [](int, const State<R>&) {});
   } else if (NS == 16 && w == 1) {
