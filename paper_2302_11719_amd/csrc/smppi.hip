@@ -567,6 +567,13 @@ static smppi_status backward_c8_t(smppi_ctx ctx, const smppi_batch* b, const C8A
   g.part = static_cast<R*>(ctx->scratch);
   g.valid = adjoint_valid(as, ctx->scratch);
   g.ck = static_cast<unsigned char*>(ctx->scratch) + as.ck_off;
+  const size_t lds_p = c8_stage_bytes<R>(a.n_max, a.t_max) + sizeof(C8AdjPipeLds<R>);
+  if (as.stored && lds_p <= (size_t)ctx->max_lds) {
+    const C8BackwardPipeArgs<R> pa{g, g.ck};
+    hipLaunchKernelGGL((k_backward_c8_pipe<R>), dim3(g.nblk_max, b->n_problems), dim3(RP_BLK), lds_p, s, pa);
+    if ((st = check_launch(ctx, "k_backward_c8_pipe"))) return st;
+    return launch_sum_partials<R>(ctx, b, as, ctx->scratch, ctx->tickets, gV, s);
+  }
   const size_t lds = c8_stage_bytes<R>(a.n_max, a.t_max) + c8_adj_lds_bytes<R>(a.t_max, g.seg_len);
   if (lds > (size_t)ctx->max_lds)
     return fail(ctx, SMPPI_ERR_SHAPE, "curvilinear adjoint needs %zu B of LDS per workgroup (device max %d)", lds,

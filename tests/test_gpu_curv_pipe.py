@@ -47,3 +47,32 @@ def test_pipelined_curvilinear_rollout_is_bit_identical(T, Ks, dtype):
         s, e = run(K)
         assert torch.equal(s, S[:K]) and torch.equal(e, eps[:K])
     assert ctx().device_errors() == 0
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-9), (torch.float32, 1e-3)])
+def test_stored_curvilinear_adjoint_vs_oracle(dtype, tol):
+    M, C = params(dtype)
+    shapes = [(1, 1), (63, 2), (64, 3), (65, 4), (130, 5), (200, 9), (129, 17)]
+    probs, tabs, x0s, db, ct, x0, wh = _setup(shapes, dtype)
+    rng = np.random.default_rng(8)
+    gs = [np.where(rng.random(p.K) < 8.0 / p.K, rng.uniform(-1, 1, p.K), 0.0) for p in probs]
+    gs[4][:64] = 0.0  # a group of 64 without upstream gradient
+    gs[4][100] = 1.0
+    gs[5][:] = 0.0  # a problem without any
+    if dtype == torch.float32:
+        gs = [g.astype(np.float32).astype(np.float64) for g in gs]
+    sig = np.array(C["sigma"])
+    for obj in (OBJ_COST, OBJ_MIXED):
+        out = core.rollout_backward_curvilinear(
+            ctx(), db, ct, M, wh, C, 11, torch.as_tensor(np.concatenate(gs), dtype=dtype, device="cuda"), obj, x0=x0)
+        for b, got in enumerate(db.controls(out)):
+            p = probs[b]
+            ref = np.zeros((p.T, 2))
+            for m in np.nonzero(gs[b])[0]:
+                eps = oracle.normals(11, b, p.it, int(m), p.T) * sig
+                ref += gs[b][m] * oracle.gradient_dual_c8(M, wh, C, *tabs[b], p.track.half_width, x0s[b], p.V, obj, eps)
+            if b == 5:
+                assert not got.any()
+            else:
+                _check_grad(got, ref, tol, (b, shapes[b], obj))
+    assert ctx().device_errors() == 0
