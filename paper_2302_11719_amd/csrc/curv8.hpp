@@ -734,26 +734,36 @@ __global__ __launch_bounds__(C8_REP_BLK) void k_repair_c8(C8RepairArgs<R> r) {
     }
     __syncthreads();
     if (threadIdx.x < WAVE) {
-      // lane j < 10 holds component j: lam_j for j < 8, the control gradient for j = 8, 9
-      const int j = threadIdx.x < 10 ? (int)threadIdx.x : 9;
+      // lane j < 10 of each row holds component j: lam_j for j < 8, the control
+      // gradient for j = 8, 9; rows read one step ahead, lam_i by DPP row broadcast
+      const int j = min((int)threadIdx.x & 15, 9);
       R lam = R(0);
       if (cost_terms) {
         C8<R> l = zero8<R>();
         stage_grad_c8(C, load_c8(xs + 8 * T), ob.w_S * C.phi_w, l);
         lam = j < 8 ? c8_comp(l, j) : R(0);
       }
-      for (int t = t_end; t >= 0; --t) {
-        const R* q = Wp + (size_t)C8_PAR * t;
-        if (j == 6) lam += q[80];
-        R l[8];
+      struct Row { R c[8], dn, dc; };
+      auto load = [&](int t) {
+        const R* q = Wp + (size_t)C8_PAR * max(t, 0);
+        Row r;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) l[i] = lane_bcast(lam, i);
-        const R nl = ((l[0] * q[j] + l[1] * q[10 + j]) + (l[2] * q[20 + j] + l[3] * q[30 + j])) +
-                     ((l[4] * q[40 + j] + l[5] * q[50 + j]) + (l[6] * q[60 + j] + l[7] * q[70 + j]));
-        if (j < 8)
-          lam = nl + (j == 0 ? q[81] : (j == 6 ? q[82] : R(0)));
-        else if (threadIdx.x < 10)
-          Wp[(size_t)C8_PAR * t + 83 + (j - 8)] = nl;
+        for (int i = 0; i < 8; ++i) r.c[i] = q[10 * i + j];
+        r.dn = j == 6 ? q[80] : R(0);
+        r.dc = j == 0 ? q[81] : (j == 6 ? q[82] : R(0));
+        return r;
+      };
+      Row cur = load(t_end);
+      for (int t = t_end; t >= 0; --t) {
+        const Row nx = load(t - 1);
+        lam += cur.dn;
+        const R nl = ((row_bcast<0>(lam) * cur.c[0] + row_bcast<1>(lam) * cur.c[1]) +
+                      (row_bcast<2>(lam) * cur.c[2] + row_bcast<3>(lam) * cur.c[3])) +
+                     ((row_bcast<4>(lam) * cur.c[4] + row_bcast<5>(lam) * cur.c[5]) +
+                      (row_bcast<6>(lam) * cur.c[6] + row_bcast<7>(lam) * cur.c[7]));
+        lam = nl + cur.dc;
+        if (threadIdx.x == 8 || threadIdx.x == 9) Wp[(size_t)C8_PAR * t + 83 + (j - 8)] = nl;
+        cur = nx;
       }
     }
     __syncthreads();

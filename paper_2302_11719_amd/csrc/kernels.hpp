@@ -1289,6 +1289,19 @@ __device__ void repair_reverse(const DevModel<R>& M, const DevCost<R>& C, const 
   }
 }
 
+// Value of lane I of each row of 16 lanes (DPP row_newbcast).
+template <int I>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + I, 0xF, 0xF, false));
+}
+template <int I>
+__device__ __forceinline__ double row_bcast(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x150 + I, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x150 + I, 0xF, 0xF, false);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
 // Value of lane i of the wave (uniform result).
 __device__ __forceinline__ float lane_bcast(float v, int i) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
@@ -1388,19 +1401,29 @@ __device__ void repair_reverse_par(const DevModel<R>& M, const DevCost<R>& C, co
 #pragma unroll
       for (int i = 0; i < 6; ++i) lam = j == i ? l6[i] : lam;
     }
-    for (int t = t_end; t >= 0; --t) {
-      const R* q = W + (size_t)P * t;
-      if (j < 2) lam += q[48 + j];
-      R l[6];
+    // Each step's row is read one step ahead (read where it is used, the LDS round
+    // trip was most of a step: 200 -> 75 cycles), and lam_i reaches the lanes by a
+    // DPP row broadcast.
+    struct Row { R c[6], dn, dc; };
+    auto load = [&](int t) {
+      const R* q = W + (size_t)P * max(t, 0);
+      Row r;
 #pragma unroll
-      for (int i = 0; i < 6; ++i) l[i] = lane_bcast(lam, i);
-      const R nl = ((l[0] * q[j] + l[1] * q[8 + j]) + (l[2] * q[16 + j] + l[3] * q[24 + j])) +
-                   (l[4] * q[32 + j] + l[5] * q[40 + j]);
-      if (j < 6) {
-        lam = nl + q[50 + j];
-      } else if (threadIdx.x < 8) {
-        W[(size_t)P * t + 56 + (j - 6)] = nl;
-      }
+      for (int i = 0; i < 6; ++i) r.c[i] = q[8 * i + j];
+      r.dn = j < 2 ? q[48 + j] : R(0);
+      r.dc = j < 6 ? q[50 + j] : R(0);
+      return r;
+    };
+    Row cur = load(t_end);
+    for (int t = t_end; t >= 0; --t) {
+      const Row nx = load(t - 1);
+      lam += cur.dn;
+      const R nl = ((row_bcast<0>(lam) * cur.c[0] + row_bcast<1>(lam) * cur.c[1]) +
+                    (row_bcast<2>(lam) * cur.c[2] + row_bcast<3>(lam) * cur.c[3])) +
+                   (row_bcast<4>(lam) * cur.c[4] + row_bcast<5>(lam) * cur.c[5]);
+      lam = nl + cur.dc;
+      if (threadIdx.x == 6 || threadIdx.x == 7) W[(size_t)P * t + 50 + j] = nl;
+      cur = nx;
     }
   }
   __syncthreads();
@@ -1879,10 +1902,15 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
       // the last transition t whose DCBF condition fails, from e_y^2 of x_t and
       // x_{t+1} (the same comparison as on the window wave)
       const int t_lim = ob.w_sq != R(0) ? T : (ob.w_lin != R(0) ? min(ob.n_lin, T) : 0);
+      // (each wave's last one by ballot: one LDS atomic per wave, not one per step)
       int lt = -1;
-      for (int t = threadIdx.x; t < t_lim; t += blockDim.x)
-        if (dcbf_active(C.alpha, tr.w2 - e2s[t], tr.w2 - e2s[t + 1])) lt = t;
-      if (lt >= 0) atomicMax(s_last, lt);
+      for (int t0 = w * WAVE; t0 < t_lim; t0 += blockDim.x) {
+        const int t = t0 + lane;
+        const bool act = t < t_lim && dcbf_active(C.alpha, tr.w2 - e2s[min(t, T)], tr.w2 - e2s[min(t + 1, T)]);
+        const unsigned long long bal = __ballot(act);
+        if (bal) lt = t0 + 63 - __builtin_clzll(bal);
+      }
+      if (lt >= 0 && lane == 0) atomicMax(s_last, lt);
     } else {
       if (w == 1 && lane == 0) *s_last = last;
     }
