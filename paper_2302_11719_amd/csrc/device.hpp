@@ -883,32 +883,33 @@ __device__ R rollout_sample(const DevModel<R>& M, const DevCost<R>& C, const Tra
 // C_f and C_r in the step's constants; the pose part needs only the stage's sine
 // and cosine, since p and psi feed nothing back into the velocities.
 template <class R>
-__device__ __forceinline__ void rk4_vjp(const DevModel<R>& M, const StepCtl<R>& c, const State<R>& x, R lam[6],
-                                        R& gd, R& gt) {
+struct VjpStage {
+  R vx, vy, om, inv, t1, tz, pa, pz, sp, cp;
+};
+// Tyre terms and heading of a stage at (X, Y, O), heading psi.
+template <class R>
+__device__ __forceinline__ VjpStage<R> vjp_stage(const DevModel<R>& M, R delta, R X, R Y, R O, R psi) {
+  VjpStage<R> g;
+  g.vx = X;
+  g.vy = Y;
+  g.om = O;
+  g.inv = rcp_r(fmax(X, M.v_min));
+  const R ta = fma_r(M.lf, O, Y) * g.inv;
+  g.tz = fma_r(M.lr, O, -Y) * g.inv;
+  const bool above = X >= M.v_min;
+  g.t1 = delta - ta;
+  g.pa = above ? ta * g.inv : R(0);
+  g.pz = above ? g.tz * g.inv : R(0);
+  sincos_r(psi, &g.sp, &g.cp);
+  return g;
+}
+// The reverse sweep over the four stages.
+template <class R>
+__device__ __forceinline__ void rk4_vjp_stages(const DevModel<R>& M, const StepCtl<R>& c, const VjpStage<R> (&g)[4],
+                                               R lam[6], R& gd, R& gt) {
   const R h = M.dt, h2 = R(0.5) * M.dt, h6 = M.dt * R(1.0 / 6.0), h3 = R(2) * h6;
   const R kz = M.lf_Iz / M.inv_m;
   const R crm = M.Cr * M.inv_m, crl = M.Cr * M.lr_Iz, csd = M.Cf * c.sd_m, ccd = M.Cf * c.cd_m;
-  R vx[4], vy[4], om[4], inv[4], t1[4], pa[4], pz[4], sp[4], cp[4];
-  vx[0] = x.vx;
-  vy[0] = x.vy;
-  om[0] = x.om;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const R X = vx[k], Y = vy[k], O = om[k];
-    inv[k] = rcp_r(fmax(X, M.v_min));
-    const R ta = fma_r(M.lf, O, Y) * inv[k], tz = fma_r(M.lr, O, -Y) * inv[k];
-    const bool above = X >= M.v_min;
-    t1[k] = c.delta - ta;
-    pa[k] = above ? ta * inv[k] : R(0);
-    pz[k] = above ? tz * inv[k] : R(0);
-    sincos_r(k == 0 ? x.psi : fma_r(k == 3 ? h : h2, om[k - 1], x.psi), &sp[k], &cp[k]);
-    if (k < 3) {
-      const R f = k == 2 ? h : h2, fc = t1[k] * ccd;
-      vx[k + 1] = fma_r(f, fma_r(Y, O, fma_r(-t1[k], csd, fma_r(-M.c_v, X, c.a_tau))), x.vx);
-      vy[k + 1] = fma_r(f, fma_r(-X, O, fma_r(tz, crm, fc)), x.vy);
-      om[k + 1] = fma_r(f, fma_r(kz, fc, -(tz * crl)), x.om);
-    }
-  }
   R op = R(0), ox = R(0), oy = R(0), oo = R(0);  // cotangent of the stage's (psi, v_x, v_y, omega)
   R ss = R(0), sx = R(0), sy = R(0), so = R(0), sg = R(0);
 #pragma unroll
@@ -918,16 +919,16 @@ __device__ __forceinline__ void rk4_vjp(const DevModel<R>& M, const StepCtl<R>& 
     const R gx = k == 3 ? w * lam[3] : fma_r(f, ox, w * lam[3]);
     const R gy = k == 3 ? w * lam[4] : fma_r(f, oy, w * lam[4]);
     const R go = k == 3 ? w * lam[5] : fma_r(f, oo, w * lam[5]);
-    const R A = w * fma_r(lam[0], cp[k], lam[1] * sp[k]), B = w * fma_r(lam[1], cp[k], -(lam[0] * sp[k]));
+    const R A = w * fma_r(lam[0], g[k].cp, lam[1] * g[k].sp), B = w * fma_r(lam[1], g[k].cp, -(lam[0] * g[k].sp));
     const R gw = fma_r(kz, go, gy);
     const R gaf = fma_r(ccd, gw, -(csd * gx)), gar = fma_r(crm, gy, -(crl * go));
-    const R g1 = inv[k] * gaf, g2 = inv[k] * gar;
-    gd = fma_r(-t1[k], fma_r(ccd, gx, csd * gw), gd + gaf);
+    const R g1 = g[k].inv * gaf, g2 = g[k].inv * gar;
+    gd = fma_r(-g[k].t1, fma_r(ccd, gx, csd * gw), gd + gaf);
     sg += gx;
-    op = fma_r(vx[k], B, -(vy[k] * A));
-    ox = fma_r(-M.c_v, gx, fma_r(-om[k], gy, fma_r(pa[k], gaf, fma_r(-pz[k], gar, A))));
-    oy = fma_r(om[k], gx, B) - (g1 + g2);
-    oo = fma_r(vy[k], gx, fma_r(-vx[k], gy, fma_r(M.lr, g2, fma_r(-M.lf, g1, gp))));
+    op = fma_r(g[k].vx, B, -(g[k].vy * A));
+    ox = fma_r(-M.c_v, gx, fma_r(-g[k].om, gy, fma_r(g[k].pa, gaf, fma_r(-g[k].pz, gar, A))));
+    oy = fma_r(g[k].om, gx, B) - (g1 + g2);
+    oo = fma_r(g[k].vy, gx, fma_r(-g[k].vx, gy, fma_r(M.lr, g2, fma_r(-M.lf, g1, gp))));
     ss += op;
     sx += ox;
     sy += oy;
@@ -938,6 +939,23 @@ __device__ __forceinline__ void rk4_vjp(const DevModel<R>& M, const StepCtl<R>& 
   lam[3] += sx;
   lam[4] += sy;
   lam[5] += so;
+}
+template <class R>
+__device__ __forceinline__ void rk4_vjp(const DevModel<R>& M, const StepCtl<R>& c, const State<R>& x, R lam[6],
+                                        R& gd, R& gt) {
+  const R h = M.dt, h2 = R(0.5) * M.dt;
+  const R kz = M.lf_Iz / M.inv_m;
+  const R crm = M.Cr * M.inv_m, crl = M.Cr * M.lr_Iz, csd = M.Cf * c.sd_m, ccd = M.Cf * c.cd_m;
+  VjpStage<R> g[4];
+  g[0] = vjp_stage(M, c.delta, x.vx, x.vy, x.om, x.psi);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const R f = k == 2 ? h : h2, X = g[k].vx, Y = g[k].vy, O = g[k].om, fc = g[k].t1 * ccd;
+    g[k + 1] = vjp_stage(M, c.delta, fma_r(f, fma_r(Y, O, fma_r(-g[k].t1, csd, fma_r(-M.c_v, X, c.a_tau))), x.vx),
+                         fma_r(f, fma_r(-X, O, fma_r(g[k].tz, crm, fc)), x.vy),
+                         fma_r(f, fma_r(kz, fc, -(g[k].tz * crl)), x.om), fma_r(f, O, x.psi));
+  }
+  rk4_vjp_stages(M, c, g, lam, gd, gt);
 }
 
 // Barrier values at a state, given the segment index at that state.

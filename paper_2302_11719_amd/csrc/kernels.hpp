@@ -1026,6 +1026,8 @@ constexpr int REP_C = 4;  // shield: control rows read ahead, segment indices st
 // respect to (x, u) (6 x 8), the local barrier/cost gradients (8) and the
 // control gradient (2).
 constexpr int REP_PAR_PER_STEP = 48 + 8 + 2;
+// Steps whose Jacobian rows the fourth wave computes at a time (six lanes each).
+constexpr int REP_AHEAD = 10;
 // Per-step constants of the shield's forward pass, one 16-byte aligned row per
 // step: the 13 values of shield_vel_row, 3 unused.
 constexpr int REP_CTL = 16;
@@ -1165,15 +1167,12 @@ __host__ __device__ inline size_t repair_lds_bytes(int t_max, int memory, bool p
 // every remaining step would be the identity after the projection already
 // applied.
 constexpr int REP_BLK = 3 * WAVE;
-// Largest workgroup of the shield kernel: the three pipeline waves, plus three
-// more for the FP32 kernel without obstacles (its registers leave room for two
-// waves per SIMD), so that the parallel reverse sweep's per-step Jacobian rows
-// (six per step) take one round instead of two for horizons up to 64.  The
-// extra waves only join the workgroup's barriers during the forward pass; the
-// launch chooses between this and REP_BLK.
+// Largest workgroup of the shield kernel: the three pipeline waves, plus one more
+// for the FP32 kernel without obstacles, which computes Jacobian rows of the reverse
+// sweep during the forward pass; the launch chooses between this and REP_BLK.
 template <class R, int NOBS>
 constexpr int rep_blk() {
-  return (sizeof(R) == 4 && NOBS == 0) ? 2 * REP_BLK : REP_BLK;
+  return (sizeof(R) == 4 && NOBS == 0) ? REP_BLK + WAVE : REP_BLK;
 }
 
 // Row-rotate of a value across the 16 lanes of each row (DPP row_ror:N).
@@ -1302,16 +1301,6 @@ __device__ __forceinline__ double row_bcast(double v) {
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// Value of lane i of the wave (uniform result).
-__device__ __forceinline__ float lane_bcast(float v, int i) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-}
-__device__ __forceinline__ double lane_bcast(double v, int i) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, i), hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 // Value of lane Q of each quad (DPP quad_perm [Q, Q, Q, Q]).
 template <int Q>
 __device__ __forceinline__ float quad_get(float v) {
@@ -1325,6 +1314,40 @@ __device__ __forceinline__ double quad_get(double v) {
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
+// Row i of [J_t^T; B_t^T], the RK4 step's transposed Jacobian with respect to (x_t,
+// u_t) for the unit cotangent e_i of x_{t+1}, into q[0..7].  vst (if not null): the
+// velocities of the step's four stages from the forward pass, else recomputed.
+template <class R>
+__device__ __forceinline__ void shield_jac_row(const DevModel<R>& M, const R* V, int T, int t, int i, const R* xs,
+                                               const R* vst, R* q) {
+  const R* pp = xs + 6 * t;
+  const R u0 = clamp_r(V[t], M.u_lo[0], M.u_hi[0]);
+  const R u1 = clamp_r(V[T + t], M.u_lo[1], M.u_hi[1]);
+  const StepCtl<R> c = step_ctl(M, u0, u1);
+  R lam[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
+#pragma unroll
+  for (int j = 0; j < 6; ++j) lam[j] = i == j ? R(1) : R(0);
+  R gd = R(0), gt = R(0);
+  if (vst) {
+    const R* gt12 = static_cast<const R*>(__builtin_assume_aligned(vst + 12 * (size_t)t, 16));
+    const R psi = pp[2];
+    VjpStage<R> g[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      g[k] = vjp_stage(M, c.delta, gt12[k], gt12[4 + k], gt12[8 + k],
+                       k == 0 ? psi : fma_r(k == 3 ? M.dt : R(0.5) * M.dt, gt12[8 + k - 1], psi));
+    rk4_vjp_stages(M, c, g, lam, gd, gt);
+  } else {
+    State<R> xp;
+    xp.px = pp[0]; xp.py = pp[1]; xp.psi = pp[2]; xp.vx = pp[3]; xp.vy = pp[4]; xp.om = pp[5];
+    rk4_vjp(M, c, xp, lam, gd, gt);
+  }
+#pragma unroll
+  for (int j = 0; j < 6; ++j) q[j] = lam[j];
+  q[6] = gd;
+  q[7] = gt;
+}
+
 // The same reverse sweep by the whole workgroup (every thread must call it).
 // The adjoint recursion is linear once the nominal trajectory is fixed:
 //   lam_t = J_t^T (lam_{t+1} + dn_t) + dc_t,   g_t = B_t^T (lam_{t+1} + dn_t),
@@ -1335,14 +1358,15 @@ __device__ __forceinline__ double quad_get(double v) {
 // recursion as 6 x 8 matrix-vector products on eight lanes of the first wave
 // (lane j forms component j from the lam_i broadcast by readlane); phase C applies the
 // projected step (or writes the gradient) for every step in parallel.
-// W: [t_max][REP_PAR_PER_STEP] LDS.
+// W: [t_max][REP_PAR_PER_STEP] LDS; the rows of the first t_done steps are there
+// already (REP_AHEAD); vst as shield_jac_row.
 template <class R, int NOBS>
 __device__ void repair_reverse_par(const DevModel<R>& M, const DevCost<R>& C, const DevObjective<R>& ob,
                                    const TrackView<R>& tr, R* V, int T, int t_end, R step, const R* xs,
-                                   const int* is, R* gout, R* W) {
+                                   const int* is, R* gout, R* W, const R* vst, int t_done) {
   constexpr int P = REP_PAR_PER_STEP;
   const bool cost_terms = ob.w_S != R(0);
-  const int n_pen = t_end + 1, nit = 6 * n_pen;
+  const int n_pen = t_end + 1, k_done = 6 * min(t_done, n_pen), nit = 6 * n_pen - k_done;
   // barrier and cost gradients of every step (dn_t, dc_t)
   auto pen_task = [&](int t) {
     const R* pp = xs + 6 * t;
@@ -1367,23 +1391,11 @@ __device__ void repair_reverse_par(const DevModel<R>& M, const DevCost<R>& C, co
   const bool own = nv > 0 && (nit + nv - 1) / nv <= (nit + nt - 1) / nt;
   const int nvt = own ? nv : nt;
   for (int k = threadIdx.x; k < nit && (int)threadIdx.x < nvt; k += nvt) {
-    const int t = k / 6, i = k % 6;
-    const R* pp = xs + 6 * t;
-    State<R> xp;
-    xp.px = pp[0]; xp.py = pp[1]; xp.psi = pp[2]; xp.vx = pp[3]; xp.vy = pp[4]; xp.om = pp[5];
-    const R u0 = clamp_r(V[t], M.u_lo[0], M.u_hi[0]);
-    const R u1 = clamp_r(V[T + t], M.u_lo[1], M.u_hi[1]);
-    R lam[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
-    lam[i] = R(1);
-    R gd = R(0), gt = R(0);
-    rk4_vjp(M, step_ctl(M, u0, u1), xp, lam, gd, gt);
-    R* q = W + (size_t)P * t + 8 * i;
-#pragma unroll
-    for (int j = 0; j < 6; ++j) q[j] = lam[j];
-    q[6] = gd;
-    q[7] = gt;
-    if (!own && i == 0) pen_task(t);
+    const int t = (k_done + k) / 6, i = (k_done + k) % 6;
+    shield_jac_row(M, V, T, t, i, xs, vst, W + (size_t)P * t + 8 * i);
   }
+  if (!own)
+    for (int t = threadIdx.x; t < n_pen; t += nt) pen_task(t);
   if (own && (int)threadIdx.x >= nv)
     for (int t = threadIdx.x - nv; t < n_pen; t += pw) pen_task(t);
   __syncthreads();
@@ -1627,6 +1639,10 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
   const DevObjective<R>& ob = a.ob;
   const bool cost_terms = ob.w_S != R(0);
   const int T = d.T, nch = (T + REP_C - 1) / REP_C;
+  // A fourth wave (its SIMD is idle during the forward pass) computes the Jacobian rows
+  // of the first t_ahead steps while the pass runs, REP_AHEAD steps at a time; the
+  // rest waits for the last active step.
+  const int t_ahead = VG && a.par_rev && blockDim.x >= 4 * WAVE ? max(0, T - REP_AHEAD / 2) / REP_AHEAD * REP_AHEAD : 0;
   const State<R> x0 = load_state(a.p.x0 + 6 * (size_t)b);
   // segment and offset at x0 do not change over the iterations
   const int idx0 = tr.idx0;
@@ -1762,6 +1778,17 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
           o[0] = x.px; o[1] = x.py; o[2] = x.psi;  // the same values from all four lanes
           wave_publish(flg + 1, t + 1);
           asm volatile("" : "+v"(x.px), "+v"(x.py), "+v"(x.psi)::"memory");
+        }
+      } else if (w == 3 && t_ahead > 0) {
+        // Jacobian rows of REP_AHEAD steps (six per step on the lanes) once the
+        // pose of the last of them is there (its stage velocities came before)
+        const int k = lane / 6, i = lane % 6;
+        int seenv = 0, seenp = 0;
+        for (int t0 = 0; t0 < t_ahead; t0 += REP_AHEAD) {
+          wave_wait(flg, t0 + REP_AHEAD - 1, seenv, a.p.err);
+          wave_wait(flg + 1, t0 + REP_AHEAD - 2, seenp, a.p.err);
+          if (k < REP_AHEAD)
+            shield_jac_row(M, Vs, T, t0 + k, i, xs, vst, wpar + (size_t)REP_PAR_PER_STEP * (t0 + k) + 8 * i);
         }
       } else if (w == 1) {
         // window wave: e_y^2, obstacle barriers and activity of each new position.
@@ -1920,7 +1947,7 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
       // gradient (zero after the last active transition), then the L-BFGS step
       for (int t = t_end + 1 + (int)threadIdx.x; t < T; t += blockDim.x) gq[t] = gq[T + t] = R(0);
       if (a.par_rev)
-        repair_reverse_par<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, gq, wpar);
+        repair_reverse_par<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, gq, wpar, VG ? vst : nullptr, t_ahead);
       else if (w == 0 && lane == 0)
         repair_reverse<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, gq);
       __syncthreads();
@@ -1934,7 +1961,8 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
       Vs[T + t] = clamp_r(Vs[T + t], M.u_lo[1], M.u_hi[1]);
     }
     if (a.par_rev) {
-      if (t_end >= 0) repair_reverse_par<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, (R*)nullptr, wpar);
+      if (t_end >= 0) repair_reverse_par<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, (R*)nullptr, wpar,
+                                                   VG ? vst : nullptr, t_ahead);
     } else if (w == 0 && lane == 0 && t_end >= 0) {
       repair_reverse<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, (R*)nullptr);
     }
@@ -1943,7 +1971,7 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
   }
 }
 
-// One workgroup per problem (rep_blk threads: three waves, or six).
+// One workgroup per problem (rep_blk threads: three waves, or four).
 template <class R, int NOBS>
 __global__ __launch_bounds__((rep_blk<R, NOBS>())) void k_repair(RepairArgs<R> a) {
   extern __shared__ __align__(16) unsigned char smem[];
