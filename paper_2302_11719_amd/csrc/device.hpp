@@ -874,88 +874,112 @@ __device__ R rollout_sample(const DevModel<R>& M, const DevCost<R>& C, const Tra
 }
 
 // ---------------------------------------------------------------- adjoint
+// Vector-Jacobian product of one derivative evaluation: given the cotangent
+// (gpx, gpy, gpsi, gvx, gvy, gom) of f's output at (psi, vx, vy, om) with the
+// step control, accumulate d/d(psi, vx, vy, om) into o* and d/d(delta, tau)
+// into gd, gt.
+template <class R>
+__device__ __forceinline__ void deriv_vjp(const DevModel<R>& M, const StepCtl<R>& c, R psi, R vx, R vy, R om,
+                                          R gpx, R gpy, R gpsi, R gvx, R gvy, R gom, R& opsi, R& ovx, R& ovy,
+                                          R& oom, R& gd, R& gt) {
+  const bool above = vx >= M.v_min;
+  const R vt = fmax(vx, M.v_min);
+  const R inv = rcp_r(vt);
+  const R Ff = M.Cf * (c.delta - (vy + M.lf * om) * inv);
+  const R Fr = M.Cr * ((M.lr * om - vy) * inv);
+  R sp, cp;
+  sincos_r(psi, &sp, &cp);
+  // kinematics
+  const R dpx = vx * cp - vy * sp, dpy = vx * sp + vy * cp;
+  opsi += gpy * dpx - gpx * dpy;
+  ovx += gpx * cp + gpy * sp;
+  ovy += gpy * cp - gpx * sp;
+  oom += gpsi;
+  // v_x equation
+  ovx += -M.c_v * gvx - om * gvy;
+  ovy += om * gvx;
+  oom += vy * gvx - vx * gvy;
+  gt += M.a_max * gvx;
+  // tyre forces
+  const R gFf = -c.sd_m * gvx + c.cd_m * gvy + c.lfcd_Iz * gom;
+  const R gFr = M.inv_m * gvy - M.lr_Iz * gom;
+  gd += -Ff * c.cd * M.inv_m * gvx - Ff * c.sd * M.inv_m * gvy - Ff * c.sd * M.lf_Iz * gom;
+  const R gaf = M.Cf * gFf, gar = M.Cr * gFr;
+  gd += gaf;
+  ovy += -inv * (gaf + gar);
+  oom += inv * (M.lr * gar - M.lf * gaf);
+  const R ginv = -(vy + M.lf * om) * gaf + (M.lr * om - vy) * gar;
+  if (above) ovx += -inv * inv * ginv;
+}
+
 // Reverse of one RK4 step from x (stage states recomputed): given lam =
 // dL/dx_{t+1}, returns dL/dx_t in lam and accumulates dL/du into gd, gt.
-//
-// Per stage k = f(X) with the cotangent w_k lam plus f times the cotangent of the
-// next stage's state (w = h/6, h/3, h/3, h/6; f = h/2, h/2, h).  The tyre terms
-// enter as t_a = (v_y + l_f om) / v, t_z = (l_r om - v_y) / v, t_1 = delta - t_a, with
-// C_f and C_r in the step's constants; the pose part needs only the stage's sine
-// and cosine, since p and psi feed nothing back into the velocities.
-template <class R>
-struct VjpStage {
-  R vx, vy, om, inv, t1, tz, pa, pz, sp, cp;
-};
-// Tyre terms and heading of a stage at (X, Y, O), heading psi.
-template <class R>
-__device__ __forceinline__ VjpStage<R> vjp_stage(const DevModel<R>& M, R delta, R X, R Y, R O, R psi) {
-  VjpStage<R> g;
-  g.vx = X;
-  g.vy = Y;
-  g.om = O;
-  g.inv = rcp_r(fmax(X, M.v_min));
-  const R ta = fma_r(M.lf, O, Y) * g.inv;
-  g.tz = fma_r(M.lr, O, -Y) * g.inv;
-  const bool above = X >= M.v_min;
-  g.t1 = delta - ta;
-  g.pa = above ? ta * g.inv : R(0);
-  g.pz = above ? g.tz * g.inv : R(0);
-  sincos_r(psi, &g.sp, &g.cp);
-  return g;
-}
-// The reverse sweep over the four stages.
-template <class R>
-__device__ __forceinline__ void rk4_vjp_stages(const DevModel<R>& M, const StepCtl<R>& c, const VjpStage<R> (&g)[4],
-                                               R lam[6], R& gd, R& gt) {
-  const R h = M.dt, h2 = R(0.5) * M.dt, h6 = M.dt * R(1.0 / 6.0), h3 = R(2) * h6;
-  const R kz = M.lf_Iz / M.inv_m;
-  const R crm = M.Cr * M.inv_m, crl = M.Cr * M.lr_Iz, csd = M.Cf * c.sd_m, ccd = M.Cf * c.cd_m;
-  R op = R(0), ox = R(0), oy = R(0), oo = R(0);  // cotangent of the stage's (psi, v_x, v_y, omega)
-  R ss = R(0), sx = R(0), sy = R(0), so = R(0), sg = R(0);
-#pragma unroll
-  for (int k = 3; k >= 0; --k) {
-    const R w = (k == 0 || k == 3) ? h6 : h3, f = k == 2 ? h : h2;
-    const R gp = k == 3 ? w * lam[2] : fma_r(f, op, w * lam[2]);
-    const R gx = k == 3 ? w * lam[3] : fma_r(f, ox, w * lam[3]);
-    const R gy = k == 3 ? w * lam[4] : fma_r(f, oy, w * lam[4]);
-    const R go = k == 3 ? w * lam[5] : fma_r(f, oo, w * lam[5]);
-    const R A = w * fma_r(lam[0], g[k].cp, lam[1] * g[k].sp), B = w * fma_r(lam[1], g[k].cp, -(lam[0] * g[k].sp));
-    const R gw = fma_r(kz, go, gy);
-    const R gaf = fma_r(ccd, gw, -(csd * gx)), gar = fma_r(crm, gy, -(crl * go));
-    const R g1 = g[k].inv * gaf, g2 = g[k].inv * gar;
-    gd = fma_r(-g[k].t1, fma_r(ccd, gx, csd * gw), gd + gaf);
-    sg += gx;
-    op = fma_r(g[k].vx, B, -(g[k].vy * A));
-    ox = fma_r(-M.c_v, gx, fma_r(-g[k].om, gy, fma_r(g[k].pa, gaf, fma_r(-g[k].pz, gar, A))));
-    oy = fma_r(g[k].om, gx, B) - (g1 + g2);
-    oo = fma_r(g[k].vy, gx, fma_r(-g[k].vx, gy, fma_r(M.lr, g2, fma_r(-M.lf, g1, gp))));
-    ss += op;
-    sx += ox;
-    sy += oy;
-    so += oo;
-  }
-  gt = fma_r(M.a_max, sg, gt);
-  lam[2] += ss;
-  lam[3] += sx;
-  lam[4] += sy;
-  lam[5] += so;
-}
 template <class R>
 __device__ __forceinline__ void rk4_vjp(const DevModel<R>& M, const StepCtl<R>& c, const State<R>& x, R lam[6],
                                         R& gd, R& gt) {
-  const R h = M.dt, h2 = R(0.5) * M.dt;
-  const R kz = M.lf_Iz / M.inv_m;
-  const R crm = M.Cr * M.inv_m, crl = M.Cr * M.lr_Iz, csd = M.Cf * c.sd_m, ccd = M.Cf * c.cd_m;
-  VjpStage<R> g[4];
-  g[0] = vjp_stage(M, c.delta, x.vx, x.vy, x.om, x.psi);
+  const R h = M.dt, h2 = R(0.5) * M.dt, h6 = M.dt * R(1.0 / 6.0);
+  R a0, a1, a3, a4, a5, b0, b1, b3, b4, b5, c0, c1, c3, c4, c5;
+  deriv(M, c, x.psi, x.vx, x.vy, x.om, a0, a1, a3, a4, a5);
+  const R a2 = x.om;
+  const R X2psi = x.psi + h2 * a2, X2vx = x.vx + h2 * a3, X2vy = x.vy + h2 * a4, X2om = x.om + h2 * a5;
+  deriv(M, c, X2psi, X2vx, X2vy, X2om, b0, b1, b3, b4, b5);
+  const R b2 = X2om;
+  const R X3psi = x.psi + h2 * b2, X3vx = x.vx + h2 * b3, X3vy = x.vy + h2 * b4, X3om = x.om + h2 * b5;
+  deriv(M, c, X3psi, X3vx, X3vy, X3om, c0, c1, c3, c4, c5);
+  const R c2 = X3om;
+  const R X4psi = x.psi + h * c2, X4vx = x.vx + h * c3, X4vy = x.vy + h * c4, X4om = x.om + h * c5;
+  // cotangents of the stage derivatives k1..k4: (h/6, h/3, h/3, h/6) * lam
+  R gk4[6], gk3[6], gk2[6], gk1[6];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const R f = k == 2 ? h : h2, X = g[k].vx, Y = g[k].vy, O = g[k].om, fc = g[k].t1 * ccd;
-    g[k + 1] = vjp_stage(M, c.delta, fma_r(f, fma_r(Y, O, fma_r(-g[k].t1, csd, fma_r(-M.c_v, X, c.a_tau))), x.vx),
-                         fma_r(f, fma_r(-X, O, fma_r(g[k].tz, crm, fc)), x.vy),
-                         fma_r(f, fma_r(kz, fc, -(g[k].tz * crl)), x.om), fma_r(f, O, x.psi));
+  for (int i = 0; i < 6; ++i) {
+    gk4[i] = h6 * lam[i];
+    gk3[i] = R(2) * h6 * lam[i];
+    gk2[i] = R(2) * h6 * lam[i];
+    gk1[i] = h6 * lam[i];
   }
-  rk4_vjp_stages(M, c, g, lam, gd, gt);
+  // k4 = f(X4): X4 = x + h k3 (p components of k feed only the output)
+  R o[4] = {R(0), R(0), R(0), R(0)};
+  deriv_vjp(M, c, X4psi, X4vx, X4vy, X4om, gk4[0], gk4[1], gk4[2], gk4[3], gk4[4], gk4[5], o[0], o[1], o[2],
+            o[3], gd, gt);
+  // psi component of k is omega of the stage state: dpsi_dot/dom = 1 (inside deriv_vjp via gpsi)
+  lam[2] += o[0];
+  lam[3] += o[1];
+  lam[4] += o[2];
+  lam[5] += o[3];
+  gk3[2] += h * o[0];
+  gk3[3] += h * o[1];
+  gk3[4] += h * o[2];
+  gk3[5] += h * o[3];
+  o[0] = o[1] = o[2] = o[3] = R(0);
+  deriv_vjp(M, c, X3psi, X3vx, X3vy, X3om, gk3[0], gk3[1], gk3[2], gk3[3], gk3[4], gk3[5], o[0], o[1], o[2],
+            o[3], gd, gt);
+  lam[2] += o[0];
+  lam[3] += o[1];
+  lam[4] += o[2];
+  lam[5] += o[3];
+  gk2[2] += h2 * o[0];
+  gk2[3] += h2 * o[1];
+  gk2[4] += h2 * o[2];
+  gk2[5] += h2 * o[3];
+  o[0] = o[1] = o[2] = o[3] = R(0);
+  deriv_vjp(M, c, X2psi, X2vx, X2vy, X2om, gk2[0], gk2[1], gk2[2], gk2[3], gk2[4], gk2[5], o[0], o[1], o[2],
+            o[3], gd, gt);
+  lam[2] += o[0];
+  lam[3] += o[1];
+  lam[4] += o[2];
+  lam[5] += o[3];
+  gk1[2] += h2 * o[0];
+  gk1[3] += h2 * o[1];
+  gk1[4] += h2 * o[2];
+  gk1[5] += h2 * o[3];
+  o[0] = o[1] = o[2] = o[3] = R(0);
+  deriv_vjp(M, c, x.psi, x.vx, x.vy, x.om, gk1[0], gk1[1], gk1[2], gk1[3], gk1[4], gk1[5], o[0], o[1], o[2],
+            o[3], gd, gt);
+  lam[2] += o[0];
+  lam[3] += o[1];
+  lam[4] += o[2];
+  lam[5] += o[3];
+  (void)a0; (void)a1; (void)b0; (void)b1; (void)c0; (void)c1;
 }
 
 // Barrier values at a state, given the segment index at that state.
@@ -969,6 +993,41 @@ __device__ __forceinline__ R track_h_at(const TrackView<R>& tr, const State<R>& 
     e2 = seg_dist2(tr, idx, x.px, x.py);
   }
   return tr.w2 - e2;
+}
+
+// Bits i0, i0 + di, ... of the obstacles whose transition from xp to xn is active
+// (r > 0, the comparison of obstacle_grad).
+template <class R>
+__device__ __forceinline__ unsigned long long obstacle_active(const DevCost<R>& C, const TrackView<R>& tr,
+                                                              const State<R>& xp, const State<R>& xn, int i0, int di) {
+  unsigned long long m = 0;
+#pragma unroll 4
+  for (int i = i0; i < tr.n_obs; i += di) {
+    const Obs<R> o = obs_at(tr, i);
+    const R pxp = xp.px - o.cx, pyp = xp.py - o.cy, pxn = xn.px - o.cx, pyn = xn.py - o.cy;
+    const R hp = pxp * pxp + pyp * pyp - o.re2, hn = pxn * pxn + pyn * pyn - o.re2;
+    if (fma_r(C.alpha, hp, -hn) > R(0)) m |= 1ull << i;
+  }
+  return m;
+}
+// Obstacle part of penalty_grad for the obstacles of mask m, in their order (the others
+// add zeros).
+template <class R>
+__device__ __forceinline__ void obstacle_grad(const DevCost<R>& C, const DevObjective<R>& ob, const TrackView<R>& tr,
+                                              const State<R>& xp, const State<R>& xn, int t, unsigned long long m,
+                                              R& lnx, R& lny, R& gpx_prev, R& gpy_prev) {
+  const R lin = (t < ob.n_lin) ? ob.w_lin : R(0);
+  for (; m; m &= m - 1) {
+    const Obs<R> o = obs_at(tr, __builtin_ctzll(m));
+    const R pxp = xp.px - o.cx, pyp = xp.py - o.cy, pxn = xn.px - o.cx, pyn = xn.py - o.cy;
+    const R hp = pxp * pxp + pyp * pyp - o.re2, hn = pxn * pxn + pyn * pyn - o.re2;
+    const R r = C.alpha * hp - hn;
+    const R g = r > R(0) ? ob.w_S * C.C_cbf + R(2) * ob.w_sq * r + lin : R(0);
+    lnx -= g * R(2) * pxn;
+    lny -= g * R(2) * pyn;
+    gpx_prev += g * C.alpha * R(2) * pxp;
+    gpy_prev += g * C.alpha * R(2) * pyp;
+  }
 }
 
 // Adds dP/dx for the transition penalty between x_t (prev) and x_{t+1} (next):

@@ -1167,13 +1167,10 @@ __host__ __device__ inline size_t repair_lds_bytes(int t_max, int memory, bool p
 // every remaining step would be the identity after the projection already
 // applied.
 constexpr int REP_BLK = 3 * WAVE;
-// Largest workgroup of the shield kernel: the three pipeline waves, plus one more
-// for the FP32 kernel without obstacles, which computes Jacobian rows of the reverse
-// sweep during the forward pass; the launch chooses between this and REP_BLK.
-template <class R, int NOBS>
-constexpr int rep_blk() {
-  return (sizeof(R) == 4 && NOBS == 0) ? REP_BLK + WAVE : REP_BLK;
-}
+// Largest workgroup of the shield kernel: the three pipeline waves, plus one that
+// computes Jacobian rows of the reverse sweep during the forward pass; the launch
+// chooses between this and REP_BLK.
+constexpr int REP_BLK_AHEAD = REP_BLK + WAVE;
 
 // Row-rotate of a value across the 16 lanes of each row (DPP row_ror:N).
 template <int N>
@@ -1314,34 +1311,32 @@ __device__ __forceinline__ double quad_get(double v) {
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
+// Or over the lanes of each quad (all of it active), the same on each lane.
+__device__ __forceinline__ unsigned quad_or(unsigned v) {
+  v |= (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // quad_perm(1,0,3,2)
+  return v | (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);  // quad_perm(2,3,0,1)
+}
+
 // Row i of [J_t^T; B_t^T], the RK4 step's transposed Jacobian with respect to (x_t,
-// u_t) for the unit cotangent e_i of x_{t+1}, into q[0..7].  vst (if not null): the
-// velocities of the step's four stages from the forward pass, else recomputed.
+// u_t) for the unit cotangent e_i of x_{t+1}, into q[0..7]; pose: (p_x, p_y, psi) of
+// x_t, vel: its velocities, vs apart.
+//
+// Its operations and their order are those of rk4_vjp's one-lane form: over long
+// horizons ten projected steps turn a last-bit change of a gradient into visibly other
+// controls (T = 92: 7e-2, L-BFGS 3e-1), so the sweep is split over lanes and waves but
+// never regrouped.
 template <class R>
-__device__ __forceinline__ void shield_jac_row(const DevModel<R>& M, const R* V, int T, int t, int i, const R* xs,
-                                               const R* vst, R* q) {
-  const R* pp = xs + 6 * t;
+__device__ __forceinline__ void shield_jac_row(const DevModel<R>& M, const R* V, int T, int t, int i, const R* pose,
+                                               const R* vel, int vs, R* q) {
+  State<R> xp;
+  xp.px = pose[0]; xp.py = pose[1]; xp.psi = pose[2]; xp.vx = vel[0]; xp.vy = vel[vs]; xp.om = vel[2 * vs];
   const R u0 = clamp_r(V[t], M.u_lo[0], M.u_hi[0]);
   const R u1 = clamp_r(V[T + t], M.u_lo[1], M.u_hi[1]);
-  const StepCtl<R> c = step_ctl(M, u0, u1);
   R lam[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
 #pragma unroll
   for (int j = 0; j < 6; ++j) lam[j] = i == j ? R(1) : R(0);
   R gd = R(0), gt = R(0);
-  if (vst) {
-    const R* gt12 = static_cast<const R*>(__builtin_assume_aligned(vst + 12 * (size_t)t, 16));
-    const R psi = pp[2];
-    VjpStage<R> g[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      g[k] = vjp_stage(M, c.delta, gt12[k], gt12[4 + k], gt12[8 + k],
-                       k == 0 ? psi : fma_r(k == 3 ? M.dt : R(0.5) * M.dt, gt12[8 + k - 1], psi));
-    rk4_vjp_stages(M, c, g, lam, gd, gt);
-  } else {
-    State<R> xp;
-    xp.px = pp[0]; xp.py = pp[1]; xp.psi = pp[2]; xp.vx = pp[3]; xp.vy = pp[4]; xp.om = pp[5];
-    rk4_vjp(M, c, xp, lam, gd, gt);
-  }
+  rk4_vjp(M, step_ctl(M, u0, u1), xp, lam, gd, gt);
 #pragma unroll
   for (int j = 0; j < 6; ++j) q[j] = lam[j];
   q[6] = gd;
@@ -1359,16 +1354,16 @@ __device__ __forceinline__ void shield_jac_row(const DevModel<R>& M, const R* V,
 // (lane j forms component j from the lam_i broadcast by readlane); phase C applies the
 // projected step (or writes the gradient) for every step in parallel.
 // W: [t_max][REP_PAR_PER_STEP] LDS; the rows of the first t_done steps are there
-// already (REP_AHEAD); vst as shield_jac_row.
+// already (REP_AHEAD).
 template <class R, int NOBS>
 __device__ void repair_reverse_par(const DevModel<R>& M, const DevCost<R>& C, const DevObjective<R>& ob,
                                    const TrackView<R>& tr, R* V, int T, int t_end, R step, const R* xs,
-                                   const int* is, R* gout, R* W, const R* vst, int t_done) {
+                                   const int* is, R* gout, R* W, int t_done) {
   constexpr int P = REP_PAR_PER_STEP;
   const bool cost_terms = ob.w_S != R(0);
   const int n_pen = t_end + 1, k_done = 6 * min(t_done, n_pen), nit = 6 * n_pen - k_done;
   // barrier and cost gradients of every step (dn_t, dc_t)
-  auto pen_task = [&](int t) {
+  auto pen_task = [&](int t, int part) {
     const R* pp = xs + 6 * t;
     State<R> xp, xn;
     xp.px = pp[0]; xp.py = pp[1]; xp.psi = pp[2]; xp.vx = pp[3]; xp.vy = pp[4]; xp.om = pp[5];
@@ -1376,7 +1371,13 @@ __device__ void repair_reverse_par(const DevModel<R>& M, const DevCost<R>& C, co
     xn.px = pn[0]; xn.py = pn[1]; xn.psi = pn[2]; xn.vx = pn[3]; xn.vy = pn[4]; xn.om = pn[5];
     R dn[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
     R gpx = R(0), gpy = R(0);
-    penalty_grad<R, NOBS>(C, ob, tr, xp, is[t], xn, is[t + 1], t, dn, gpx, gpy);
+    penalty_grad<R, 0>(C, ob, tr, xp, is[t], xn, is[t + 1], t, dn, gpx, gpy);
+    if constexpr (NOBS > 0) {  // four lanes test a quarter of the obstacles each
+      const unsigned long long m = obstacle_active(C, tr, xp, xn, part, 4);
+      const unsigned long long lo = quad_or((unsigned)m), hi = quad_or((unsigned)(m >> 32));
+      if (part) return;
+      obstacle_grad(C, ob, tr, xp, xn, t, lo | hi << 32, dn[0], dn[1], gpx, gpy);
+    }
     R dc[6] = {gpx, gpy, R(0), R(0), R(0), R(0)};
     if (cost_terms) stage_grad(C, tr, xp, is[t], ob.w_S, dc);
     R* dd = W + (size_t)P * t + 48;
@@ -1385,19 +1386,21 @@ __device__ void repair_reverse_par(const DevModel<R>& M, const DevCost<R>& C, co
 #pragma unroll
     for (int j = 0; j < 6; ++j) dd[2 + j] = dc[j];
   };
-  // The gradient tasks take waves of their own when the Jacobian rows then need
-  // no more rounds (else each wave would run both kinds of task in turn).
-  const int nt = blockDim.x, pw = WAVE * ((n_pen + WAVE - 1) / WAVE), nv = nt - pw;
+  // The gradient tasks (PL lanes per step) take waves of their own when the Jacobian
+  // rows then need no more rounds (else each wave would run both kinds of task in
+  // turn).
+  constexpr int PL = NOBS > 0 ? 4 : 1;
+  const int nt = blockDim.x, pw = min(nt, WAVE * ((PL * n_pen + WAVE - 1) / WAVE)), nv = nt - pw;
   const bool own = nv > 0 && (nit + nv - 1) / nv <= (nit + nt - 1) / nt;
   const int nvt = own ? nv : nt;
   for (int k = threadIdx.x; k < nit && (int)threadIdx.x < nvt; k += nvt) {
     const int t = (k_done + k) / 6, i = (k_done + k) % 6;
-    shield_jac_row(M, V, T, t, i, xs, vst, W + (size_t)P * t + 8 * i);
+    shield_jac_row(M, V, T, t, i, xs + 6 * t, xs + 6 * t + 3, 1, W + (size_t)P * t + 8 * i);
   }
   if (!own)
-    for (int t = threadIdx.x; t < n_pen; t += nt) pen_task(t);
+    for (int k = threadIdx.x; k < PL * n_pen; k += nt) pen_task(k / PL, k % PL);
   if (own && (int)threadIdx.x >= nv)
-    for (int t = threadIdx.x - nv; t < n_pen; t += pw) pen_task(t);
+    for (int k = threadIdx.x - nv; k < PL * n_pen; k += pw) pen_task(k / PL, k % PL);
   __syncthreads();
   if (threadIdx.x < WAVE) {
     // lane j < 8 holds component j: lam_j for j < 6, the control gradient for j = 6, 7;
@@ -1782,13 +1785,17 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
       } else if (w == 3 && t_ahead > 0) {
         // Jacobian rows of REP_AHEAD steps (six per step on the lanes) once the
         // pose of the last of them is there (its stage velocities came before)
-        const int k = lane / 6, i = lane % 6;
+        const int k = lane / 6;
         int seenv = 0, seenp = 0;
         for (int t0 = 0; t0 < t_ahead; t0 += REP_AHEAD) {
           wave_wait(flg, t0 + REP_AHEAD - 1, seenv, a.p.err);
           wave_wait(flg + 1, t0 + REP_AHEAD - 2, seenp, a.p.err);
-          if (k < REP_AHEAD)
-            shield_jac_row(M, Vs, T, t0 + k, i, xs, vst, wpar + (size_t)REP_PAR_PER_STEP * (t0 + k) + 8 * i);
+          const int t = t0 + k;
+          int i = lane % 6;
+          asm volatile("" : "+v"(i));  // (same basic block as its uses: see shield_jac_row)
+          if (k < REP_AHEAD)  // (the states' velocities are still in the stages' rows)
+            shield_jac_row(M, Vs, T, t, i, xs + 6 * t, vst + 12 * (size_t)t, 4,
+                           wpar + (size_t)REP_PAR_PER_STEP * t + 8 * i);
         }
       } else if (w == 1) {
         // window wave: e_y^2, obstacle barriers and activity of each new position.
@@ -1947,7 +1954,7 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
       // gradient (zero after the last active transition), then the L-BFGS step
       for (int t = t_end + 1 + (int)threadIdx.x; t < T; t += blockDim.x) gq[t] = gq[T + t] = R(0);
       if (a.par_rev)
-        repair_reverse_par<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, gq, wpar, VG ? vst : nullptr, t_ahead);
+        repair_reverse_par<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, gq, wpar, t_ahead);
       else if (w == 0 && lane == 0)
         repair_reverse<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, gq);
       __syncthreads();
@@ -1961,8 +1968,7 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
       Vs[T + t] = clamp_r(Vs[T + t], M.u_lo[1], M.u_hi[1]);
     }
     if (a.par_rev) {
-      if (t_end >= 0) repair_reverse_par<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, (R*)nullptr, wpar,
-                                                   VG ? vst : nullptr, t_ahead);
+      if (t_end >= 0) repair_reverse_par<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, (R*)nullptr, wpar, t_ahead);
     } else if (w == 0 && lane == 0 && t_end >= 0) {
       repair_reverse<R, NOBS>(M, C, ob, tr, Vs, T, t_end, a.step, xs, is, (R*)nullptr);
     }
@@ -1971,9 +1977,9 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
   }
 }
 
-// One workgroup per problem (rep_blk threads: three waves, or four).
+// One workgroup per problem (three waves, or four).
 template <class R, int NOBS>
-__global__ __launch_bounds__((rep_blk<R, NOBS>())) void k_repair(RepairArgs<R> a) {
+__global__ __launch_bounds__(REP_BLK_AHEAD) void k_repair(RepairArgs<R> a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_last;
   const int b = blockIdx.x;
