@@ -8,7 +8,9 @@ any other implementation: if the shared library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
+import struct
 import threading
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -157,6 +159,8 @@ class SmppiError(RuntimeError):
 def lib():
     """Load libsmppi.so (built by __graft_entry__.build()); raises if it is missing."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -174,21 +178,26 @@ def lib():
     return _lib
 
 
+_model_items = operator.itemgetter("m", "lf", "lr", "Iz", "Cf", "Cr", "a_max", "c_v", "v_min", "dt")
+_cost_items = operator.itemgetter("v_g", "q_v", "q_ey", "C_obs", "phi_w", "lambda_u")
+_cost_items_end = operator.itemgetter("C_cbf", "gamma")
+
+
+_model_pack = struct.Struct("14d").pack  # the fields of Model and Cost, doubles throughout
+_cost_pack = struct.Struct("10d").pack
+
+
+# (packed in one call: field by field, the two structures took 10 us of a call whose
+# caches are cold, as between the steps of a learning loop)
 def model_struct(d: dict) -> Model:
-    m = Model()
-    for k in ("m", "lf", "lr", "Iz", "Cf", "Cr", "a_max", "c_v", "v_min", "dt"):
-        setattr(m, k, float(d[k]))
-    m.u_lo[0], m.u_lo[1] = d["u_lo"]
-    m.u_hi[0], m.u_hi[1] = d["u_hi"]
-    return m
+    lo0, lo1 = d["u_lo"]
+    hi0, hi1 = d["u_hi"]
+    return Model.from_buffer_copy(_model_pack(*map(float, _model_items(d)), lo0, lo1, hi0, hi1))
 
 
 def cost_struct(d: dict) -> Cost:
-    c = Cost()
-    for k in ("v_g", "q_v", "q_ey", "C_obs", "phi_w", "lambda_u", "C_cbf", "gamma"):
-        setattr(c, k, float(d[k]))
-    c.sigma[0], c.sigma[1] = d["sigma"]
-    return c
+    s0, s1 = d["sigma"]
+    return Cost.from_buffer_copy(_cost_pack(*map(float, _cost_items(d)), s0, s1, *map(float, _cost_items_end(d))))
 
 
 def wheels_struct(d: dict) -> Wheels:

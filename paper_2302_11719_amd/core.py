@@ -17,11 +17,13 @@ from ._lib import SmppiError
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream's handle, without building the Stream object around it (2.7 us
+    of an 11 us call, 8 to 16 us with cold caches)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _p(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 class Context:
@@ -149,7 +151,7 @@ def rollout(ctx: Context, db: DeviceBatch, model: dict, cost: dict, seed: int, n
     st = L.lib().smppi_rollout(ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)),
                                ctypes.byref(L.cost_struct(cost)), ctypes.byref(_noise(seed, nominal)),
                                ctypes.byref(db.track), _p(db.x0 if x0 is None else x0), _p(db.V if V is None else V),
-                               _p(db.iter if iters is None else iters), _p(S), _p(eps), ctypes.c_void_p(_stream()))
+                               _p(db.iter if iters is None else iters), _p(S), _p(eps), _stream())
     ctx.check(st, "smppi_rollout")
     return (S, eps.view(db.sum_K, db.t_max, 2)) if want_eps else S
 
@@ -181,7 +183,7 @@ def rollout_curvilinear(ctx: Context, db: DeviceBatch, ct: CurvTrackArrays, mode
                                            ctypes.byref(_noise(seed, nominal)), ctypes.byref(ct.track),
                                            _p(db.x0 if x0 is None else x0), _p(db.V if V is None else V),
                                            _p(db.iter if iters is None else iters), _p(S), _p(eps),
-                                           ctypes.c_void_p(_stream()))
+                                           _stream())
     ctx.check(st, "smppi_rollout_curvilinear")
     return (S, eps.view(db.sum_K, db.t_max, 2)) if want_eps else S
 
@@ -196,7 +198,7 @@ def rollout_backward_curvilinear(ctx: Context, db: DeviceBatch, ct: CurvTrackArr
         ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)), ctypes.byref(L.wheels_struct(wheels)),
         ctypes.byref(L.cost_struct(cost)), ctypes.byref(_noise(seed, nominal)), ctypes.byref(ct.track),
         _p(db.x0 if x0 is None else x0), _p(db.V if V is None else V), _p(db.iter if iters is None else iters),
-        _p(grad_S), ctypes.byref(L.objective_struct(objective)), _p(out), ctypes.c_void_p(_stream()))
+        _p(grad_S), ctypes.byref(L.objective_struct(objective)), _p(out), _stream())
     ctx.check(st, "smppi_rollout_backward_curvilinear")
     return out
 
@@ -210,7 +212,7 @@ def shield_repair_curvilinear(ctx: Context, db: DeviceBatch, ct: CurvTrackArrays
     st = L.lib().smppi_shield_repair_curvilinear(
         ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)), ctypes.byref(L.wheels_struct(wheels)),
         ctypes.byref(L.cost_struct(cost)), ctypes.byref(ct.track), _p(db.x0 if x0 is None else x0), _p(V_plus),
-        ctypes.byref(opts), _p(out), ctypes.c_void_p(_stream()))
+        ctypes.byref(opts), _p(out), _stream())
     ctx.check(st, "smppi_shield_repair_curvilinear")
     return out
 
@@ -222,7 +224,7 @@ def execute_curvilinear(ctx: Context, db: DeviceBatch, ct: CurvTrackArrays, mode
     st = L.lib().smppi_execute_curvilinear(ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)),
                                            ctypes.byref(L.wheels_struct(wheels)), ctypes.byref(ct.track), _p(V_exec),
                                            _p(V_plus), _p(dist), int(n_dist), _p(db.x0), _p(db.V), _p(db.iter),
-                                           ctypes.c_void_p(_stream()))
+                                           _stream())
     ctx.check(st, "smppi_execute_curvilinear")
 
 
@@ -231,7 +233,7 @@ def weights(ctx: Context, db: DeviceBatch, S: torch.Tensor, lam: float):
     w = torch.empty_like(S)
     stats = torch.empty(4 * db.B, dtype=db.dtype, device=db.device)
     st = L.lib().smppi_weights(ctx.h, ctypes.byref(db.batch), _p(S), float(lam), _p(w), _p(stats),
-                               ctypes.c_void_p(_stream()))
+                               _stream())
     ctx.check(st, "smppi_weights")
     return w, stats.view(db.B, 4)
 
@@ -244,7 +246,7 @@ def update(ctx: Context, db: DeviceBatch, model: dict, cost: dict, seed: int, w:
     ctx.reserve(db)
     st = L.lib().smppi_update(ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)),
                               ctypes.byref(L.cost_struct(cost)), ctypes.byref(_noise(seed, nominal)), _p(V), _p(w),
-                              _p(db.iter if iters is None else iters), _p(out), ctypes.c_void_p(_stream()))
+                              _p(db.iter if iters is None else iters), _p(out), _stream())
     ctx.check(st, "smppi_update")
     return out
 
@@ -266,7 +268,7 @@ def rollout_backward(ctx: Context, db: DeviceBatch, model: dict, cost: dict, see
         ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)), ctypes.byref(L.cost_struct(cost)),
         ctypes.byref(_noise(seed, nominal)), ctypes.byref(db.track), _p(db.x0 if x0 is None else x0), _p(V),
         _p(db.iter if iters is None else iters), _p(grad_S), ctypes.byref(L.objective_struct(objective)), _p(out),
-        ctypes.c_void_p(_stream()))
+        _stream())
     ctx.check(st, name)
     return out
 
@@ -280,7 +282,7 @@ def shield_repair(ctx: Context, db: DeviceBatch, model: dict, cost: dict, V_plus
     st = L.lib().smppi_shield_repair(ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)),
                                      ctypes.byref(L.cost_struct(cost)), ctypes.byref(db.track),
                                      _p(db.x0 if x0 is None else x0), _p(V_plus), ctypes.byref(opts), _p(out),
-                                     ctypes.c_void_p(_stream()))
+                                     _stream())
     ctx.check(st, "smppi_shield_repair")
     return out
 
@@ -291,7 +293,7 @@ def execute(ctx: Context, db: DeviceBatch, model: dict, V_exec: torch.Tensor, V_
     st = L.lib().smppi_execute(ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)), _p(V_exec),
                                _p(V_plus), _p(dist), int(n_dist), _p(db.x0 if x is None else x),
                                _p(db.V if V is None else V), _p(db.iter if iters is None else iters),
-                               ctypes.c_void_p(_stream()))
+                               _stream())
     ctx.check(st, "smppi_execute")
 
 
@@ -336,10 +338,10 @@ class Plan:
         self.h = h
 
     def launch(self):
-        self.ctx.check(L.lib().smppi_plan_launch(self.h, ctypes.c_void_p(_stream())), "smppi_plan_launch")
+        self.ctx.check(L.lib().smppi_plan_launch(self.h, _stream()), "smppi_plan_launch")
 
     def launch_profiled(self):
-        self.ctx.check(L.lib().smppi_plan_launch_profiled(self.h, ctypes.c_void_p(_stream())),
+        self.ctx.check(L.lib().smppi_plan_launch_profiled(self.h, _stream()),
                        "smppi_plan_launch_profiled")
 
     def stage_ms(self):
@@ -382,7 +384,7 @@ def debug_philox(ctx: Context, ctr: np.ndarray, key) -> np.ndarray:
     dc = torch.as_tensor(ctr.view(np.int32), device=f"cuda:{ctx.device}")
     out = torch.empty_like(dc)
     k = (ctypes.c_uint32 * 2)(int(key[0]) & 0xFFFFFFFF, int(key[1]) & 0xFFFFFFFF)
-    st = L.lib().smppi_debug_philox(ctx.h, _p(dc), k, n, _p(out), ctypes.c_void_p(_stream()))
+    st = L.lib().smppi_debug_philox(ctx.h, _p(dc), k, n, _p(out), _stream())
     ctx.check(st, "smppi_debug_philox")
     torch.cuda.synchronize()
     return out.cpu().numpy().view(np.uint32)
