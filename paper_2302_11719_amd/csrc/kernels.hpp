@@ -462,6 +462,7 @@ struct UpdateArgs {
   R* part;            // [B][nblk_max][2][t_max]
   uint32_t* tickets;  // [B], zero between calls
   int nblk_max;
+  int spw;            // samples per workgroup, at most UPD_BLOCK
 };
 
 constexpr int UPD_BLOCK = 256;
@@ -620,11 +621,11 @@ __global__ __launch_bounds__(UPD_BLOCK) void k_update(UpdateArgs<R> a) {
       for (int i = threadIdx.x; i < 2 * d.T; i += blockDim.x) Vpb[i] = Vb[i];
     return;
   }
-  const int nblk = (d.K + UPD_BLOCK - 1) / UPD_BLOCK;
+  const int nblk = (d.K + a.spw - 1) / a.spw;
   if ((int)blockIdx.x >= nblk) return;
-  const int m = blockIdx.x * UPD_BLOCK + threadIdx.x;
+  const int m = blockIdx.x * a.spw + threadIdx.x;
   const int ms[1] = {m};
-  const R ws[1] = {(m < d.K) ? a.w[d.k0 + m] : R(0)};
+  const R ws[1] = {((int)threadIdx.x < a.spw && m < d.K) ? a.w[d.k0 + m] : R(0)};
   R* gp = a.part + ((size_t)b * a.nblk_max + blockIdx.x) * 2 * a.p.t_max;
   block_noise_sums<R, UPD_BLOCK, 1>(a.M, a.C, a.p.seed, (uint32_t)(a.p.pid_base + b), a.p.iter[b],
                                     a.p.nominal != 0, Vb, d.T, ms, ws, L, gp);

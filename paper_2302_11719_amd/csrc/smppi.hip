@@ -96,14 +96,33 @@ AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
   return a;
 }
 
+// Scratch of an update with spw samples per workgroup.
+static size_t update_bytes(const smppi_batch* b, int spw) {
+  const size_t r = b->dtype == SMPPI_F32 ? sizeof(float) : sizeof(double);
+  const size_t k = (size_t)std::max(0, b->k_max);
+  return r * (size_t)b->n_problems * std::max<size_t>(1, (k + spw - 1) / spw) * 2 * (size_t)b->t_max;
+}
+// Samples per workgroup of an update.  An FP64 normal takes some 1000 cycles, so few
+// FP64 samples go over many workgroups, until the workgroups' tickets and the last one's
+// sum over their partials (0.1 us each) take longer than the normals: 32 samples up to 64
+// workgroups, 64 up to 128.  K = 256, T = 20: 15.1 -> 8.0 us; K = 1000, T = 50: 21.1 ->
+// 9.7; K = 4096, T = 50: 21.7 -> 13.7 (32 samples: 16.9); K = 8192: 22.9 -> 18.6;
+// K = 16384 stays at 24.6 (64 samples: 30).  FP32 normals are cheap and most FP32 weights
+// are zero, which the 256-sample workgroup skips: 7.2 us up to K = 8192.
+static int update_samples(const smppi_batch* b) {
+  const auto wgs = [&](int spw) { return ((size_t)std::max(0, b->k_max) + spw - 1) / spw * (size_t)b->n_problems; };
+  if (b->dtype == SMPPI_F64 && wgs(32) <= 64) return 32;
+  if (b->dtype == SMPPI_F64 && wgs(64) <= 128) return 64;
+  return UPD_BLOCK;
+}
+
 // Scratch of the plain calls for a batch within these host bounds: the
 // update's per-workgroup partials [B][workgroups][2][t_max], the adjoint's
 // (adjoint_scratch) and, for FP32 rollouts with obstacles, the padded obstacle
 // slots [B][64].
 size_t smppi::batch_scratch_bytes(const smppi_batch* b) {
-  const size_t r = b->dtype == SMPPI_F32 ? sizeof(float) : sizeof(double);
-  const size_t B = (size_t)b->n_problems, k = (size_t)std::max(0, b->k_max), t = (size_t)b->t_max;
-  const size_t upd = r * B * std::max<size_t>(1, (k + UPD_BLOCK - 1) / UPD_BLOCK) * 2 * t;
+  const size_t B = (size_t)b->n_problems;
+  const size_t upd = update_bytes(b, update_samples(b));
   const AdjScratch adj = adjoint_scratch(b);
   const size_t bwd = adj.pad_off + adj.pad_bytes;
   const size_t pad = b->dtype == SMPPI_F32 ? sizeof(float4) * B * kMaxObs : 0;
@@ -742,11 +761,11 @@ static smppi_status update_t(smppi_ctx ctx, const smppi_batch* b, const smppi_mo
   a.V = static_cast<const R*>(V);
   a.w = static_cast<const R*>(w);
   a.V_plus = static_cast<R*>(Vp);
-  a.nblk_max = std::max(1, (b->k_max + UPD_BLOCK - 1) / UPD_BLOCK);
+  a.spw = update_samples(b);
+  if (update_bytes(b, a.spw) > ctx->scratch_bytes) a.spw = UPD_BLOCK;  // reserved for another batch
+  a.nblk_max = std::max(1, (b->k_max + a.spw - 1) / a.spw);
   smppi_status st;
-  if ((st = need_scratch(ctx, sizeof(R) * (size_t)b->n_problems * a.nblk_max * 2 * b->t_max, b->n_problems,
-                         "smppi_update")))
-    return st;
+  if ((st = need_scratch(ctx, update_bytes(b, a.spw), b->n_problems, "smppi_update"))) return st;
   a.part = static_cast<R*>(ctx->scratch);
   a.tickets = ctx->tickets;
   hipLaunchKernelGGL((k_update<R>), dim3(a.nblk_max, b->n_problems), dim3(UPD_BLOCK), 0, s, a);
