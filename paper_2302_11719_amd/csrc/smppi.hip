@@ -413,6 +413,18 @@ static smppi_status launch_rollout(smppi_ctx ctx, const smppi_batch* b, const Ro
                        reinterpret_cast<const float*>(a.p.obs), a.p.obs_max, NOBS, (float)a.C.alpha, pad);
     if ((st = check_launch(ctx, "k_pad_obs"))) return st;
     ra.obs_pad = pad;
+    if constexpr (NOBS > 0 && sizeof(R) == 4) {
+      // The step pipeline up to six workgroups of 64 samples per compute unit (T = 50:
+      // K = 4096 57.8 -> 32.5 us, 65536 58.3 -> 48.4, 98304 76.8 -> 68.0; at 131072 it
+      // takes 84.9 against 77.1 with one wave per 64 samples)
+      const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
+      const size_t l64 = lds + sizeof(ObsPipeLds);
+      if (n64 <= 6 * ctx->n_cu && l64 <= (size_t)ctx->max_lds) {
+        hipLaunchKernelGGL((k_rollout_pipe_obs<NOBS>), dim3((b->k_max + 63) / 64, b->n_problems), dim3(RP_BLK), l64,
+                           s, ra);
+        return check_launch(ctx, "k_rollout_pipe_obs");
+      }
+    }
   }
   hipLaunchKernelGGL((k_rollout<R, NOBS>), dim3(gx, b->n_problems), dim3(blk), lds, s, ra);
   return check_launch(ctx, "k_rollout");
