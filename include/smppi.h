@@ -200,8 +200,8 @@ int smppi_abi_version(void);
  * bounds of `batch` (n_problems, k_max, t_max, dtype; its device arrays are not
  * read): the update's and the adjoint's per-workgroup partials
  * (dtype bytes x B x ceil(k_max / workgroup samples) x 2 x t_max), the adjoint's
- * stored states or checkpoints (see smppi_rollout_backward), the padded
- * obstacle slots of FP32 rollouts (B x 64 x 16 bytes) and B ticket counters.
+ * stored states or checkpoints (see smppi_rollout_backward), 64 rows of
+ * obstacles per problem (FP32, B x 64 x 16 bytes) and B ticket counters.
  * Allocates (and synchronises) only when the ctx holds less; the scratch never
  * shrinks.  Call it before smppi_rollout (FP32 with obstacles), smppi_update
  * and smppi_rollout_backward, outside timed or captured regions. */
@@ -225,10 +225,8 @@ smppi_status smppi_device_errors(smppi_ctx ctx, uint32_t* flags);
  * iter: device [B] uint32 iteration counters (noise counter word 3).
  * eps_out: NULL, or device [sum K][t_max][2] dtype receiving the effective
  *   noise u - v of every step (debug/test; rows beyond T_b untouched).
- * FP32 with obstacles: a small kernel first copies every problem's obstacles
- * into padded slots in the ctx scratch (B * 64 * 16 bytes, see
- * smppi_reserve_batch), which the rollout kernel reads through the scalar
- * cache. */
+ * FP32 with obstacles: needs B * 64 * 16 bytes of ctx scratch (see
+ * smppi_reserve_batch). */
 smppi_status smppi_rollout(smppi_ctx ctx, const smppi_batch* batch, const smppi_model* model,
                            const smppi_cost* cost, const smppi_noise* noise, const smppi_track* track,
                            const void* x0, const void* V, const uint32_t* iter, void* S, void* eps_out,
@@ -399,9 +397,7 @@ smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batch, const sm
                                smppi_plan* out);
 /* One MPPI iteration of every problem: rollout, weights and update fused in one
  * persistent launch, then (optionally) the shield and the execute/warm start.
- * With obstacles outside latency mode, a small kernel first copies the current
- * obstacles into padded slots the plan owns (one slot per lane of each wave
- * of the rollouts). */
+ * The obstacles are read at every launch, so they may move in between. */
 smppi_status smppi_plan_launch(smppi_plan plan, void* stream);
 void smppi_plan_destroy(smppi_plan plan);
 /* Profiling: the same work as smppi_plan_launch, enqueued without the graph and

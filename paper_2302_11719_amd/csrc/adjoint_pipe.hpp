@@ -77,7 +77,7 @@ __device__ __forceinline__ R track_e2_grad(const TrackView<R>& tr, R px, R py, i
   return e2;
 }
 
-// Obstacle slots staged in LDS: FP32 reads its obstacles per wave from the padded slots.
+// Obstacle slots staged in LDS: FP32 reads its obstacles per wave (wave_obstacles).
 template <class R>
 __host__ __device__ inline int adj_pipe_obs(int obs_max) {
   return sizeof(R) == 4 ? 0 : obs_max;
@@ -123,7 +123,7 @@ struct RevBarrier {
     pnx = xT.px;
     pny = xT.py;
     hn = tr.w2 - track_e2_grad(tr, pnx, pny, xT.idx, gnx, gny);
-    if constexpr (NOBS > 0 && sizeof(R) == 4) wob = WaveObstacles(a.obs_pad + (size_t)b * NOBS, NOBS);
+    if constexpr (NOBS > 0 && sizeof(R) == 4) wob = wave_obstacles(a.p, b, (float)C.alpha);
   }
   __device__ __forceinline__ Quad<R> step(int t) {
     const In n2 = load(t - 2);

@@ -598,10 +598,6 @@ struct WaveObstacles {
   float4 mine;  // slot of obstacle `lane` (inert beyond the table)
 
   __device__ __forceinline__ WaveObstacles() : mine(make_float4(0.f, 0.f, -1e30f, 0.f)) {}
-  __device__ __forceinline__ WaveObstacles(const float4* slots, int n_slots) {
-    const int lane = threadIdx.x % WAVE;
-    mine = lane < n_slots ? slots[lane] : make_float4(0.f, 0.f, -1e30f, 0.f);
-  }
 
   // Obstacles that may contribute to some lane's transition into a point of the
   // per-lane box [xlo, xhi] x [ylo, yhi] (order-preserving keys) by a step of at

@@ -279,6 +279,23 @@ __device__ R block_min(R v, R* red) {
   return s;
 }
 
+// The obstacles of a problem for a wave of FP32 samples, from the caller's rows
+// (c_x, c_y, (r + margin)^2, r^2): one row per lane, kappa = (1 - alpha) ((r + margin)^2 -
+// r^2).  (A kernel of its own that wrote padded slots took 4.5 us of every launch, and
+// in a plan the graph of two kernels.)  The offsets are read here and not taken from
+// ProblemDims: a one-problem plan keeps those from its creation.
+template <class R>
+__device__ __forceinline__ WaveObstacles wave_obstacles(const ProblemArgs<R>& p, int b, float alpha) {
+  WaveObstacles w;
+  const int lane = threadIdx.x % WAVE;
+  const int o0 = p.obs_off ? p.obs_off[b] : 0, no = p.obs_off ? p.obs_off[b + 1] - o0 : 0;
+  if (no <= p.obs_max && lane < no) {
+    const float* o = reinterpret_cast<const float*>(p.obs) + 4 * ((size_t)o0 + lane);
+    w.mine = make_float4(o[0], o[1], o[3], (1.f - alpha) * (o[2] - o[3]));
+  }
+  return w;
+}
+
 // ============================================================== rollout
 template <class R>
 struct RolloutArgs {
@@ -288,30 +305,7 @@ struct RolloutArgs {
   const R* V;
   R* S;
   R* eps_out;
-  const float4* obs_pad;  // FP32 with obstacles: [B][NOBS] slots from k_pad_obs (WaveObstacles)
 };
-
-// Obstacle slots of every problem for the FP32 rollouts and adjoint
-// (WaveObstacles): (c_x, c_y, r^2, (1 - alpha) ((r + margin)^2 - r^2)) for
-// the problem's obstacles, the inert slot (0, 0, -1e30, 0) after them, n_slots
-// per problem.  Runs before every launch that reads them, so obstacles the caller
-// moves between launches are seen.  A problem whose obstacle count is out of
-// range gets inert slots only (the rollout kernels flag and skip it).
-// Grid: one workgroup per problem.
-static __global__ void k_pad_obs(const int32_t* __restrict__ obs_off, const float* __restrict__ obs, int obs_max,
-                          int n_slots, float alpha, float4* __restrict__ out) {
-  const int b = blockIdx.x;
-  const int o0 = obs_off ? obs_off[b] : 0, no = obs_off ? obs_off[b + 1] - o0 : 0;
-  const bool ok = no >= 0 && no <= obs_max;
-  for (int i = threadIdx.x; i < n_slots; i += blockDim.x) {
-    float4 v = make_float4(0.f, 0.f, -1e30f, 0.f);
-    if (ok && i < no) {
-      const float* o = obs + 4 * ((size_t)o0 + i);
-      v = make_float4(o[0], o[1], o[3], (1.f - alpha) * (o[2] - o[3]));
-    }
-    out[(size_t)b * n_slots + i] = v;
-  }
-}
 
 template <class R, int NOBS>
 __global__ __launch_bounds__(256) void k_rollout(RolloutArgs<R> a) {
@@ -341,7 +335,7 @@ __global__ __launch_bounds__(256) void k_rollout(RolloutArgs<R> a) {
   R* eo = (a.eps_out && own) ? a.eps_out + (size_t)(d.k0 + m) * a.p.t_max * 2 : nullptr;
   R s;
   if constexpr (WV)
-    s = rollout_sample<R, NOBS>(a.M, a.C, tr, x0, Vs, d.T, ns, eo, WaveObstacles(a.obs_pad + (size_t)b * NOBS, NOBS));
+    s = rollout_sample<R, NOBS>(a.M, a.C, tr, x0, Vs, d.T, ns, eo, wave_obstacles(a.p, b, a.C.alpha));
   else
     s = rollout_sample<R, NOBS>(a.M, a.C, tr, x0, Vs, d.T, ns, eo);
   if (own) a.S[d.k0 + m] = s;
@@ -718,14 +712,12 @@ __host__ __device__ inline size_t adj_lds_bytes(int /*t_max*/, int seg_len) {
 // Reverse sweep of one lane's trajectory.  `V` is [2][T] in LDS.  For every t
 // (descending) calls sink(t, dL/dv_{t,0}, dL/dv_{t,1}); the sink may modify V[t]
 // (the repair does), which is safe because V[t'] for t' >= t is never read again.
-// FP32 with obstacles: `slots` (k_pad_obs) gives the obstacle transitions
+// FP32 with obstacles: `wob` (wave_obstacles) gives the obstacle transitions
 // for the whole wave (WaveObstacles::grad) instead of the LDS table.
 template <class R, int NOBS, class Sink>
 __device__ void adjoint_lane(const DevModel<R>& M, const DevCost<R>& C, const DevObjective<R>& ob,
                              const TrackView<R>& tr, const State<R>& x0, R* V, int T, NoiseStream<R>& ns,
-                             const AdjLds<R>& L, int seg_len, int lane, Sink& sink, const float4* slots = nullptr) {
-  WaveObstacles wob;  // FP32 with obstacles: this lane's slot, read once
-  if constexpr (NOBS > 0 && sizeof(R) == sizeof(float)) wob = WaveObstacles(slots, NOBS);
+                             const AdjLds<R>& L, int seg_len, int lane, Sink& sink, const WaveObstacles& wob) {
   // forward with checkpoints
   State<R> x = x0;
   int idx = tr.idx0;
@@ -815,7 +807,6 @@ struct BackwardArgs {
   R* part;            // [B][nblk_max][2][t_max]: per-workgroup partials, summed by k_sum_partials
   uint32_t* valid;    // [B]: 1 when the problem's sizes are valid (written by workgroup 0)
   unsigned char* ck;  // [B][nblk_max] blocks of adj_ck_bytes_per_wg(t_max, seg_len, 6): checkpoints
-  const float4* obs_pad;  // FP32 with obstacles: [B][NOBS] slots from k_pad_obs (WaveObstacles)
   int nblk_max;
   int seg_len;
 };
@@ -882,7 +873,7 @@ __global__ __launch_bounds__(WAVE) void k_backward(BackwardArgs<R> a) {
   sink.lane = lane;
   const State<R> x0 = load_state(a.p.x0 + 6 * (size_t)b);
   adjoint_lane<R, NOBS>(a.M, a.C, a.ob, tr, x0, Vs, d.T, ns, L, a.seg_len, lane, sink,
-                        a.obs_pad ? a.obs_pad + (size_t)b * NOBS : nullptr);
+                        NOBS > 0 && sizeof(R) == 4 ? wave_obstacles(a.p, b, (float)a.C.alpha) : WaveObstacles());
 }
 
 // Sum of the adjoint's per-workgroup partials: out[2 t0_b + i] = sum over the

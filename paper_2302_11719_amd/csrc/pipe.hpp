@@ -395,7 +395,7 @@ __global__ __launch_bounds__(RP_BLK) void k_rollout_pipe(RolloutArgs<R> a) {
 // pairs with one obstacle live set, as rollout_sample does, with the same operations in
 // the same order (and the same multiply-adds, hence two forms of the speed term).  Bound
 // by the RK4 wave up to one workgroup per compute unit, by issue beyond: K = 65536,
-// T = 100, 64 obstacles 111 -> 88 us, K = 32768 111 -> 62 us.
+// T = 100, 64 obstacles 109 -> 85 us, K = 32768 108 -> 59 us.
 struct ObsPipeLds {
   RolloutPipe<float, 64>::Lds p;  // cnt[3]: offsets written
   float ey2[RolloutPipe<float, 64>::D][64];
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(RP_BLK) void k_rollout_pipe_obs(RolloutArgs<float> 
       wave_publish(&P.cnt[3], t + 1);
     }
   } else {
-    const WaveObstacles os(a.obs_pad + (size_t)b * NOBS, NOBS);
+    const WaveObstacles os = wave_obstacles(a.p, b, a.C.alpha);
     int idx = tr.idx0, seen = 0;
     float ey2 = lateral_sq(tr, x0.px, x0.py, idx);
     float h0 = tr.w2 - ey2, vx = x0.vx, px = x0.px, py = x0.py;

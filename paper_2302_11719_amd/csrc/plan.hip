@@ -12,8 +12,7 @@
 // plan executes, the plant step and warm start, all in the same launch (a
 // separate shield kernel when the workgroup has fewer than three waves or its
 // LDS does not fit; a separate execute kernel without the shield).  A launch
-// of several kernels (obstacle slots, empty problems, separate shield or
-// execute) is captured once into a HIP graph; a single kernel is launched
+// of several kernels (empty problems, separate shield or execute) is captured once into a HIP graph; a single kernel is launched
 // directly.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
@@ -55,7 +54,6 @@ struct FusedArgs {
   uint32_t* exits;           // [1] workgroups that have left the tile loop
   int repair;                // nonzero: the combining workgroup also runs the shield (and execute)
   RepairArgs<float> rep;
-  const float4* obs_pad;     // [B][kMaxObs] obstacle slots (WaveObstacles; NOBS > 0, tile mode)
   // One-problem plans: problem 0's dimensions, taken from the offsets at plan
   // creation (checked there); tile k is then (0, k), and a workgroup reads
   // neither the tile list nor the offsets before staging.
@@ -406,7 +404,7 @@ __global__ __launch_bounds__(BLK) void k_fused(FusedArgs a) {
     } else {
       // (with obstacles every lane of a wave that has samples runs: the wave-level
       // obstacle evaluation needs the whole wave; lanes past K copy the last sample)
-      const WaveObstacles wob = NOBS > 0 ? WaveObstacles(a.obs_pad + (size_t)b * NOBS, NOBS) : WaveObstacles();
+      const WaveObstacles wob = NOBS > 0 ? wave_obstacles(a.p, b, a.C.alpha) : WaveObstacles();
 #pragma unroll
       for (int j = 0; j < SPT; ++j) {
         ms[j] = kb * a.tile + j * BLK + tid;
@@ -715,7 +713,6 @@ struct smppi_plan_s {
   int32_t* tile_off = nullptr;
   float* part = nullptr;
   uint32_t* counters = nullptr;  // [0] queue, [1..B] tickets, [B+1] exits
-  float4* obs_pad = nullptr;     // [B][kMaxObs] obstacle slots (tile mode with obstacles)
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -756,11 +753,6 @@ static smppi_status plan_enqueue(smppi_plan p, hipStream_t s, bool profiled = fa
                        static_cast<const float*>(p->bufs.V), static_cast<float*>(p->bufs.V_plus),
                        static_cast<float*>(p->bufs.stats));
     if ((st = check_launch(ctx, "k_copy_empty"))) return st;
-  }
-  if (p->obs_pad && p->fa.n_tiles > 0) {
-    hipLaunchKernelGGL(k_pad_obs, dim3(B), dim3(kMaxObs), 0, s, static_cast<const int32_t*>(p->track.obs_off),
-                       static_cast<const float*>(p->track.obs), p->fa.p.obs_max, kMaxObs, p->fa.C.alpha, p->obs_pad);
-    if ((st = check_launch(ctx, "k_pad_obs"))) return st;
   }
   if (p->fa.n_tiles > 0) {
     if (profiled)  // events stamped with the kernel's own start and end
@@ -803,7 +795,6 @@ extern "C" void smppi_plan_destroy(smppi_plan p) {
   if (p->tile_off) (void)hipFree(p->tile_off);
   if (p->part) (void)hipFree(p->part);
   if (p->counters) (void)hipFree(p->counters);
-  if (p->obs_pad) (void)hipFree(p->obs_pad);
   delete p;
 }
 
@@ -926,10 +917,6 @@ extern "C" smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batc
     return bail(hip_fail(ctx, e, "hipMemcpy(tile_off)"));
   if ((e = hipMemset(p->counters, 0, sizeof(uint32_t) * (B + 2))) != hipSuccess)
     return bail(hip_fail(ctx, e, "hipMemset(counters)"));
-  // tile mode with obstacles reads them from padded slots (one per lane of each wave)
-  if (!pipe && obs_slots(track) > 0 &&
-      (e = hipMalloc(&p->obs_pad, sizeof(float4) * (size_t)B * kMaxObs)) != hipSuccess)
-    return bail(hip_fail(ctx, e, "hipMalloc(obs_pad)"));
 
   FusedArgs& a = p->fa;
   a.p = problem_args<float>(ctx, &p->batch, &p->track, &p->noise, bufs->x0, bufs->iter);
@@ -971,7 +958,6 @@ extern "C" smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batc
   a.queue = p->counters;
   a.tickets = p->counters + 1;
   a.exits = p->counters + 1 + B;
-  a.obs_pad = p->obs_pad;
   p->lds = (int)stage_lds_bytes<float>(track->poly_max, batch->t_max, obs_slots(track));
   hipFuncAttributes fattr{};
   if ((e = hipFuncGetAttributes(&fattr, reinterpret_cast<const void*>(fn))) != hipSuccess)
@@ -1017,7 +1003,7 @@ extern "C" smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batc
   p->grid = grid;
   // A graph only pays when the launch has several kernels; a single kernel is
   // launched directly (measured: the one-node graph adds about 4 us per launch).
-  const int n_kernels = (any_empty ? 1 : 0) + (n_tiles > 0 ? (p->obs_pad ? 2 : 1) : 0) + (opts->repair && !p->fused_shield ? 1 : 0) +
+  const int n_kernels = (any_empty ? 1 : 0) + (n_tiles > 0 ? 1 : 0) + (opts->repair && !p->fused_shield ? 1 : 0) +
                         (opts->execute && !opts->repair ? 1 : 0);
   if (opts->use_graph && n_kernels > 1) {
     if ((e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking)) != hipSuccess)

@@ -88,7 +88,7 @@ AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
                  (a.r == sizeof(float) ? adj_rows_bytes_per_wg<float>(b->t_max) : adj_rows_bytes_per_wg<double>(b->t_max));
   a.stored = a.rows_bytes <= max_rows;
   if (a.stored) a.ck_bytes = std::max(a.ck_bytes, a.rows_bytes);
-  // padded obstacle slots of the FP32 adjoint ([B][64] float4), after the checkpoints
+  // (64 rows of obstacles per problem are part of the documented reservation)
   a.pad_off = (a.ck_off + a.ck_bytes + 255) & ~(size_t)255;
   a.pad_bytes = b->dtype == SMPPI_F32 ? sizeof(float4) * (size_t)b->n_problems * kMaxObs : 0;
   a.tickets = (size_t)b->n_problems * a.n_chunks;
@@ -383,8 +383,6 @@ static smppi_status launch_rollout(smppi_ctx ctx, const smppi_batch* b, const Ro
   const int gx = b->k_max > 0 ? (b->k_max + blk - 1) / blk : 0;
   if (gx == 0) return SMPPI_OK;
   const size_t lds = stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, a.p.obs_max);
-  RolloutArgs<R> ra = a;
-  ra.obs_pad = nullptr;
   if constexpr (NOBS == 0) {
     // Few samples: the step pipeline (same bits).  16 samples per workgroup up to
     // two workgroups per compute unit (K = 4096, T = 50: FP32 50.7 -> 22.8 us, FP64
@@ -396,37 +394,29 @@ static smppi_status launch_rollout(smppi_ctx ctx, const smppi_batch* b, const Ro
     const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
     const size_t l16 = lds + sizeof(typename RolloutPipe<R, 16>::Lds), l64 = lds + sizeof(typename RolloutPipe<R, 64>::Lds);
     if (n16 <= 2 * ctx->n_cu && l16 <= (size_t)ctx->max_lds) {
-      hipLaunchKernelGGL((k_rollout_pipe<R, 16>), dim3((b->k_max + 15) / 16, b->n_problems), dim3(RP_BLK), l16, s, ra);
+      hipLaunchKernelGGL((k_rollout_pipe<R, 16>), dim3((b->k_max + 15) / 16, b->n_problems), dim3(RP_BLK), l16, s, a);
       return check_launch(ctx, "k_rollout_pipe");
     }
     if (n64 <= (sizeof(R) == 4 ? 4 : 2) * ctx->n_cu && l64 <= (size_t)ctx->max_lds) {
-      hipLaunchKernelGGL((k_rollout_pipe<R, 64>), dim3((b->k_max + 63) / 64, b->n_problems), dim3(RP_BLK), l64, s, ra);
+      hipLaunchKernelGGL((k_rollout_pipe<R, 64>), dim3((b->k_max + 63) / 64, b->n_problems), dim3(RP_BLK), l64, s, a);
       return check_launch(ctx, "k_rollout_pipe");
     }
   }
-  if (NOBS > 0 && sizeof(R) == 4) {
-    // FP32 obstacles are evaluated per wave from padded slots in the scratch buffer
+  if constexpr (NOBS > 0 && sizeof(R) == 4) {
+    // (the documented reservation; the kernels read the caller's rows)
     smppi_status st = need_scratch(ctx, sizeof(float4) * (size_t)b->n_problems * NOBS, 0, "smppi_rollout");
     if (st) return st;
-    float4* pad = static_cast<float4*>(ctx->scratch);
-    hipLaunchKernelGGL(k_pad_obs, dim3(b->n_problems), dim3(64), 0, s, a.p.obs_off,
-                       reinterpret_cast<const float*>(a.p.obs), a.p.obs_max, NOBS, (float)a.C.alpha, pad);
-    if ((st = check_launch(ctx, "k_pad_obs"))) return st;
-    ra.obs_pad = pad;
-    if constexpr (NOBS > 0 && sizeof(R) == 4) {
-      // The step pipeline up to six workgroups of 64 samples per compute unit (T = 50:
-      // K = 4096 57.8 -> 32.5 us, 65536 58.3 -> 48.4, 98304 76.8 -> 68.0; at 131072 it
-      // takes 84.9 against 77.1 with one wave per 64 samples)
-      const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
-      const size_t l64 = lds + sizeof(ObsPipeLds);
-      if (n64 <= 6 * ctx->n_cu && l64 <= (size_t)ctx->max_lds) {
-        hipLaunchKernelGGL((k_rollout_pipe_obs<NOBS>), dim3((b->k_max + 63) / 64, b->n_problems), dim3(RP_BLK), l64,
-                           s, ra);
-        return check_launch(ctx, "k_rollout_pipe_obs");
-      }
+    // The step pipeline up to six workgroups of 64 samples per compute unit (T = 50:
+    // K = 4096 55.2 -> 29.9 us, 65536 55.9 -> 45.9, 98304 74.1 -> 65.1; at 131072 it
+    // takes 82.3 against 73.4 with one wave per 64 samples)
+    const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
+    const size_t l64 = lds + sizeof(ObsPipeLds);
+    if (n64 <= 6 * ctx->n_cu && l64 <= (size_t)ctx->max_lds) {
+      hipLaunchKernelGGL((k_rollout_pipe_obs<NOBS>), dim3((b->k_max + 63) / 64, b->n_problems), dim3(RP_BLK), l64, s, a);
+      return check_launch(ctx, "k_rollout_pipe_obs");
     }
   }
-  hipLaunchKernelGGL((k_rollout<R, NOBS>), dim3(gx, b->n_problems), dim3(blk), lds, s, ra);
+  hipLaunchKernelGGL((k_rollout<R, NOBS>), dim3(gx, b->n_problems), dim3(blk), lds, s, a);
   return check_launch(ctx, "k_rollout");
 }
 
@@ -837,18 +827,8 @@ static smppi_status backward_launch(smppi_ctx ctx, const smppi_batch* b, const s
   a.part = static_cast<R*>(scratch);
   a.valid = adjoint_valid(as, scratch);
   a.ck = static_cast<unsigned char*>(scratch) + as.ck_off;
-  a.obs_pad = nullptr;
-  smppi_status st;
-  if (t->obs_max > 0 && sizeof(R) == sizeof(float)) {
-    // FP32 obstacles per wave, from padded slots (as the rollout)
-    float4* pad = reinterpret_cast<float4*>(static_cast<unsigned char*>(scratch) + as.pad_off);
-    hipLaunchKernelGGL(k_pad_obs, dim3(b->n_problems), dim3(64), 0, s, a.p.obs_off,
-                       reinterpret_cast<const float*>(a.p.obs), a.p.obs_max, kMaxObs, (float)a.C.alpha, pad);
-    if ((st = check_launch(ctx, "k_pad_obs"))) return st;
-    a.obs_pad = pad;
-  }
-  st = t->obs_max > 0 ? launch_backward<R, kMaxObs>(ctx, b, a, as.stored, s)
-                      : launch_backward<R, 0>(ctx, b, a, as.stored, s);
+  smppi_status st = t->obs_max > 0 ? launch_backward<R, kMaxObs>(ctx, b, a, as.stored, s)
+                                   : launch_backward<R, 0>(ctx, b, a, as.stored, s);
   if (st) return st;
   return launch_sum_partials<R>(ctx, b, as, scratch, tickets, gV, s);
 }
