@@ -92,6 +92,10 @@ smppi_status repair_t(smppi_ctx ctx, const smppi_batch* b, const smppi_model* m,
                       const smppi_track* t, const void* x0, const void* Vp, const smppi_repair_opts* o, void* Vs,
                       hipStream_t s, hipEvent_t kernel_start = nullptr, hipEvent_t kernel_stop = nullptr,
                       const ExecFuse* ex = nullptr);
+// Tile-mode plans: whether their rollouts are faster as a launch of the step pipeline
+// before the fused kernel, and that launch (e0: event stamped with its start).
+bool plan_rollout_pays(smppi_ctx ctx, const smppi_batch* b, const ProblemArgs<float>& p);
+smppi_status plan_rollout(smppi_ctx ctx, const smppi_batch* b, const RolloutArgs<float>& a, hipStream_t s, hipEvent_t e0);
 template <class R>
 smppi_status execute_t(smppi_ctx ctx, const smppi_batch* b, const smppi_model* m, const void* Ve, const void* Vp,
                        const void* dist, int32_t n_dist, void* x, void* V, uint32_t* iter, hipStream_t s);

@@ -331,7 +331,8 @@ __device__ float rollout_pipe(const FusedArgs& a, const TrackView<float>& tr, co
 // FUSE: the shield (and execute) code is compiled in (plans that run the shield
 // inside the launch); without it the kernel needs far fewer registers, which
 // raises the occupancy of plans without the shield.
-template <int NOBS, int BLK, int SPT, bool PIPE, bool FUSE>
+// GIVEN: S is there already (the rollouts were a launch of their own).
+template <int NOBS, int BLK, int SPT, bool PIPE, bool FUSE, bool GIVEN = false>
 __global__ __launch_bounds__(BLK) void k_fused(FusedArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   // block reductions: minima in red[0, waves), sums in red[waves, 4 waves); a
@@ -382,7 +383,12 @@ __global__ __launch_bounds__(BLK) void k_fused(FusedArgs a) {
       if (!load_dims(a.p, b, d)) continue;
     }
     if (b != staged_b) {
-      tr = stage_problem(a.p, b, d, a.V, smem, &Vs);
+      if constexpr (GIVEN) {  // the controls are all that is left to read
+        Vs = reinterpret_cast<float*>(smem);
+        for (int i = tid; i < 2 * d.T; i += BLK) Vs[i] = a.V[2 * (size_t)d.t0 + i];
+      } else {
+        tr = stage_problem(a.p, b, d, a.V, smem, &Vs);
+      }
       staged_b = b;
       __syncthreads();
     }
@@ -393,7 +399,15 @@ __global__ __launch_bounds__(BLK) void k_fused(FusedArgs a) {
     int ms[SPT];
     bool own[SPT];
     float mn = INFINITY;
-    if constexpr (PIPE) {
+    if constexpr (GIVEN) {
+#pragma unroll
+      for (int j = 0; j < SPT; ++j) {
+        ms[j] = kb * a.tile + j * BLK + tid;
+        own[j] = ms[j] < d.K;
+        s[j] = own[j] ? a.S[d.k0 + ms[j]] : INFINITY;
+        if (isfinite(s[j])) mn = fminf(mn, s[j]);
+      }
+    } else if constexpr (PIPE) {
       __shared__ PipeLds PL;
       ms[0] = kb * a.tile + tid % WAVE;
       own[0] = tid < WAVE && ms[0] < d.K;
@@ -535,7 +549,7 @@ __global__ __launch_bounds__(BLK) void k_fused(FusedArgs a) {
       const int n4 = (2 * d.T + 3) >> 2;
       const bool wide = !PIPE && one_pass && n4 <= BLK && ntb > 16 * G;
       if (wide) {
-        constexpr int NB4 = 8;  // loads in flight (no more registers than the rollout needs)
+        constexpr int NB4 = GIVEN ? 16 : 8;  // loads in flight (no more registers than the rollout needs)
         const int G4 = BLK / n4, g4 = tid / n4, i4 = tid % n4;
         float a4[4] = {0.f, 0.f, 0.f, 0.f};
         if (g4 < G4) {
@@ -708,6 +722,7 @@ struct smppi_plan_s {
   int grid = 0, block = 256, lds = 0;
   bool any_empty = false;
   bool fused_shield = false;  // shield (+ execute) run inside k_fused
+  bool given = false;         // rollouts as a launch of their own before k_fused
   // device allocations owned by the plan
   int2* tiles = nullptr;
   int32_t* tile_off = nullptr;
@@ -755,8 +770,18 @@ static smppi_status plan_enqueue(smppi_plan p, hipStream_t s, bool profiled = fa
     if ((st = check_launch(ctx, "k_copy_empty"))) return st;
   }
   if (p->fa.n_tiles > 0) {
-    if (profiled)  // events stamped with the kernel's own start and end
-      hipExtLaunchKernelGGL(p->fn, dim3(p->grid), dim3(p->block), (uint32_t)p->lds, s, p->ek[0], p->ek[1], 0u, p->fa);
+    if (p->given) {
+      RolloutArgs<float> ra{};
+      ra.p = p->fa.p;
+      ra.M = p->fa.M;
+      ra.C = p->fa.C;
+      ra.V = p->fa.V;
+      ra.S = p->fa.S;
+      if ((st = plan_rollout(ctx, &p->batch, ra, s, profiled ? p->ek[0] : nullptr))) return st;
+    }
+    if (profiled)  // events stamped with the kernels' own start and end
+      hipExtLaunchKernelGGL(p->fn, dim3(p->grid), dim3(p->block), (uint32_t)p->lds, s, p->given ? nullptr : p->ek[0],
+                            p->ek[1], 0u, p->fa);
     else
       hipLaunchKernelGGL(p->fn, dim3(p->grid), dim3(p->block), p->lds, s, p->fa);
     if ((st = check_launch(ctx, "k_fused"))) return st;
@@ -864,7 +889,12 @@ extern "C" smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batc
     if (pipe) return track->obs_max > 0 ? pick_pipe<kMaxObs>(fuse) : pick_pipe<0>(fuse);
     return track->obs_max > 0 ? pick_fused<kMaxObs>(block, spt, fuse) : pick_fused<0>(block, spt, fuse);
   };
-  FusedFn fn = pick(false);
+  // (unless a configuration was asked for) the rollouts as a step pipeline of their own
+  // where that is faster; S has the same bits
+  const bool given = !pipe && !want_fuse && spt == 1 && opts->pipeline == 0 && opts->block == 0 && opts->tile == 0 &&
+                     opts->grid == 0 &&
+                     plan_rollout_pays(ctx, batch, problem_args<float>(ctx, batch, track, noise, bufs->x0, bufs->iter));
+  FusedFn fn = given ? k_fused<0, 256, 1, false, false, true> : pick(false);
   if (!fn) return fail(ctx, SMPPI_ERR_UNSUPPORTED, "no fused kernel for block %d, tile %d", block, tile);
   std::vector<int32_t> ntile(B), tile_off(B + 1, 0);
   bool any_empty = false;
@@ -901,6 +931,7 @@ extern "C" smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batc
   p->block = block;
   p->fn = fn;
   p->any_empty = any_empty;
+  p->given = given;
   auto bail = [&](smppi_status s2) {
     smppi_plan_destroy(p);
     return s2;

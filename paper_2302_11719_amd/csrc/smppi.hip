@@ -377,47 +377,62 @@ extern "C" smppi_status smppi_device_errors(smppi_ctx ctx, uint32_t* flags) {
 }
 
 // ------------------------------------------------------------------ rollout
+// Few samples run as a step pipeline (the same bits): samples per workgroup, or 0.
+// Without obstacles, 16 samples per workgroup up to two workgroups per compute unit
+// (K = 4096, T = 50: FP32 50.7 -> 22.8 us, FP64 127 -> 31.7; at 16384 it takes 30.3 /
+// 79.6 against 23.9 / 58.2 with 64); 64 samples up to four per unit in FP32 and two in
+// FP64 (K = 65536, T = 100, FP32: 98.9 -> 77.7 us; at 131072, T = 50: 76.4 against 63.6
+// with one wave per 64 samples, FP64 at 65536: 165.9 against 128.7).  FP32 with
+// obstacles: 64 samples up to six per unit (T = 50: K = 4096 55.2 -> 29.9 us, 65536
+// 55.9 -> 45.9, 98304 74.1 -> 65.1; at 131072 it takes 82.3 against 73.4).
 template <class R, int NOBS>
-static smppi_status launch_rollout(smppi_ctx ctx, const smppi_batch* b, const RolloutArgs<R>& a, hipStream_t s) {
-  const int blk = 256;
-  const int gx = b->k_max > 0 ? (b->k_max + blk - 1) / blk : 0;
-  if (gx == 0) return SMPPI_OK;
-  const size_t lds = stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, a.p.obs_max);
+static int rollout_pipe_samples(smppi_ctx ctx, const smppi_batch* b, const ProblemArgs<R>& p) {
+  const size_t lds = stage_lds_bytes<R>(p.poly_max, p.t_max, p.obs_max), max = (size_t)ctx->max_lds;
+  const int64_t n16 = (int64_t)b->n_problems * ((b->k_max + 15) / 16);
+  const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
+  if (NOBS > 0) return sizeof(R) == 4 && n64 <= 6 * ctx->n_cu && lds + sizeof(ObsPipeLds) <= max ? 64 : 0;
+  if (n16 <= 2 * ctx->n_cu && lds + sizeof(typename RolloutPipe<R, 16>::Lds) <= max) return 16;
+  if (n64 <= (sizeof(R) == 4 ? 4 : 2) * ctx->n_cu && lds + sizeof(typename RolloutPipe<R, 64>::Lds) <= max) return 64;
+  return 0;
+}
+
+// e0 (if not null): event stamped with the kernel's own start.
+template <class R, int NOBS>
+static smppi_status launch_rollout(smppi_ctx ctx, const smppi_batch* b, const RolloutArgs<R>& a, hipStream_t s,
+                                   hipEvent_t e0 = nullptr) {
+  if (b->k_max <= 0) return SMPPI_OK;
+  const int ns = rollout_pipe_samples<R, NOBS>(ctx, b, a.p), blk = ns ? RP_BLK : 256, per = ns ? ns : blk;
+  size_t lds = stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, a.p.obs_max);
+  void (*fn)(RolloutArgs<R>) = k_rollout<R, NOBS>;
   if constexpr (NOBS == 0) {
-    // Few samples: the step pipeline (same bits).  16 samples per workgroup up to
-    // two workgroups per compute unit (K = 4096, T = 50: FP32 50.7 -> 22.8 us, FP64
-    // 127 -> 31.7; at 16384 it takes 30.3 / 79.6 against 23.9 / 58.2 with 64); 64
-    // samples up to four per unit in FP32 and two in FP64 (K = 65536, T = 100, FP32:
-    // 98.9 -> 77.7 us; at 131072, T = 50: 76.4 against 63.6 with one wave per 64
-    // samples, FP64 at 65536: 165.9 against 128.7).
-    const int64_t n16 = (int64_t)b->n_problems * ((b->k_max + 15) / 16);
-    const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
-    const size_t l16 = lds + sizeof(typename RolloutPipe<R, 16>::Lds), l64 = lds + sizeof(typename RolloutPipe<R, 64>::Lds);
-    if (n16 <= 2 * ctx->n_cu && l16 <= (size_t)ctx->max_lds) {
-      hipLaunchKernelGGL((k_rollout_pipe<R, 16>), dim3((b->k_max + 15) / 16, b->n_problems), dim3(RP_BLK), l16, s, a);
-      return check_launch(ctx, "k_rollout_pipe");
-    }
-    if (n64 <= (sizeof(R) == 4 ? 4 : 2) * ctx->n_cu && l64 <= (size_t)ctx->max_lds) {
-      hipLaunchKernelGGL((k_rollout_pipe<R, 64>), dim3((b->k_max + 63) / 64, b->n_problems), dim3(RP_BLK), l64, s, a);
-      return check_launch(ctx, "k_rollout_pipe");
-    }
+    if (ns == 16) fn = k_rollout_pipe<R, 16>;
+    if (ns == 64) fn = k_rollout_pipe<R, 64>;
+    if (ns) lds += ns == 16 ? sizeof(typename RolloutPipe<R, 16>::Lds) : sizeof(typename RolloutPipe<R, 64>::Lds);
+  } else if constexpr (sizeof(R) == 4) {
+    if (ns) fn = k_rollout_pipe_obs<NOBS>;
+    if (ns) lds += sizeof(ObsPipeLds);
   }
-  if constexpr (NOBS > 0 && sizeof(R) == 4) {
-    // (the documented reservation; the kernels read the caller's rows)
-    smppi_status st = need_scratch(ctx, sizeof(float4) * (size_t)b->n_problems * NOBS, 0, "smppi_rollout");
-    if (st) return st;
-    // The step pipeline up to six workgroups of 64 samples per compute unit (T = 50:
-    // K = 4096 55.2 -> 29.9 us, 65536 55.9 -> 45.9, 98304 74.1 -> 65.1; at 131072 it
-    // takes 82.3 against 73.4 with one wave per 64 samples)
-    const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
-    const size_t l64 = lds + sizeof(ObsPipeLds);
-    if (n64 <= 6 * ctx->n_cu && l64 <= (size_t)ctx->max_lds) {
-      hipLaunchKernelGGL((k_rollout_pipe_obs<NOBS>), dim3((b->k_max + 63) / 64, b->n_problems), dim3(RP_BLK), l64, s, a);
-      return check_launch(ctx, "k_rollout_pipe_obs");
-    }
-  }
-  hipLaunchKernelGGL((k_rollout<R, NOBS>), dim3(gx, b->n_problems), dim3(blk), lds, s, a);
-  return check_launch(ctx, "k_rollout");
+  const dim3 grid((b->k_max + per - 1) / per, b->n_problems);
+  if (e0)
+    hipExtLaunchKernelGGL(fn, grid, dim3(blk), (uint32_t)lds, s, e0, nullptr, 0u, a);
+  else
+    hipLaunchKernelGGL(fn, grid, dim3(blk), lds, s, a);
+  return check_launch(ctx, ns ? "k_rollout_pipe" : "k_rollout");
+}
+
+// A tile-mode plan runs its rollouts in the pipeline's own launch wherever there is one
+// (K = 65536, T = 100: 115 -> 94 us, with obstacles 126 -> 102; K = 4096, T = 50 with
+// obstacles 66 -> 40; 16 x 4096, T = 50: 68 -> 61), except short horizons of many samples,
+// where the second launch takes more than it gives (K = 65000, T = 10: 28.8 against 30.8;
+// T = 20: 39.3 -> 37.8).
+bool smppi::plan_rollout_pays(smppi_ctx ctx, const smppi_batch* b, const ProblemArgs<float>& p) {
+  const int ns = p.obs_max > 0 ? rollout_pipe_samples<float, kMaxObs>(ctx, b, p) : rollout_pipe_samples<float, 0>(ctx, b, p);
+  const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
+  return ns > 0 && (p.t_max >= 16 || n64 <= 2 * ctx->n_cu);
+}
+smppi_status smppi::plan_rollout(smppi_ctx ctx, const smppi_batch* b, const RolloutArgs<float>& a, hipStream_t s,
+                                 hipEvent_t e0) {
+  return a.p.obs_max > 0 ? launch_rollout<float, kMaxObs>(ctx, b, a, s, e0) : launch_rollout<float, 0>(ctx, b, a, s, e0);
 }
 
 template <class R>
@@ -431,6 +446,11 @@ static smppi_status rollout_t(smppi_ctx ctx, const smppi_batch* b, const smppi_m
   a.V = static_cast<const R*>(V);
   a.S = static_cast<R*>(S);
   a.eps_out = static_cast<R*>(eps_out);
+  if (t->obs_max > 0 && b->k_max > 0 && sizeof(R) == sizeof(float)) {
+    // (the documented reservation; the kernels read the caller's rows)
+    const smppi_status st = need_scratch(ctx, sizeof(float4) * (size_t)b->n_problems * kMaxObs, 0, "smppi_rollout");
+    if (st) return st;
+  }
   if (t->obs_max > 0) return launch_rollout<R, kMaxObs>(ctx, b, a, s);
   return launch_rollout<R, 0>(ctx, b, a, s);
 }
