@@ -458,16 +458,25 @@ __global__ __launch_bounds__(BLK) void k_fused(FusedArgs a) {
     block_sum3<float, false>(z, q, nf, red_sum);
     const int toff_b = a.one ? 0 : a.tile_off[b];  // first tile of problem b
     float* P = a.part + (size_t)(toff_b + kb) * pstride;
-    block_noise_sums<float, BLK, SPT, PIPE>(a.M, a.C, a.p.seed, pid, it, a.p.nominal != 0, Vs, d.T, ms, om, L,
-                                      P + PART_HDR);
+    // (several samples per thread: batches of many tiles per compute unit)
+    constexpr bool THROUGH = SPT == 1;
+    block_noise_sums<float, BLK, SPT, PIPE, THROUGH>(a.M, a.C, a.p.seed, pid, it, a.p.nominal != 0, Vs, d.T, ms, om, L,
+                                                     P + PART_HDR);
     if (tid == 0) {
-      P[0] = mn;
-      P[1] = z;
-      P[2] = q;
-      P[3] = nf;
+      if constexpr (THROUGH) {
+        store_agent(P, mn);
+        store_agent(P + 1, z);
+        store_agent(P + 2, q);
+        store_agent(P + 3, nf);
+      } else {
+        P[0] = mn;
+        P[1] = z;
+        P[2] = q;
+        P[3] = nf;
+      }
     }
     // ---- ticket; the last tile of problem b combines
-    ticket_release();
+    ticket_release<THROUGH>();
     __syncthreads();
     const int ntb = (d.K + a.tile - 1) / a.tile;
     if (tid == 0) s_ticket = atomicAdd(&a.tickets[b], 1u);
