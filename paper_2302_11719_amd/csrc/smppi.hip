@@ -96,6 +96,14 @@ AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
   return a;
 }
 
+// The layout a call uses: every state stored if the ctx holds that much, else
+// checkpoints (a ctx reserved for a batch beyond kMaxRows holds no stored states, but
+// its checkpoints cover those of every smaller batch).
+static AdjScratch adjoint_layout(smppi_ctx ctx, const smppi_batch* b) {
+  const AdjScratch as = adjoint_scratch(b);
+  return as.pad_off + as.pad_bytes <= ctx->scratch_bytes ? as : adjoint_scratch(b, 0);
+}
+
 // Scratch of an update with spw samples per workgroup.
 static size_t update_bytes(const smppi_batch* b, int spw) {
   const size_t r = b->dtype == SMPPI_F32 ? sizeof(float) : sizeof(double);
@@ -599,7 +607,7 @@ static smppi_status backward_c8_t(smppi_ctx ctx, const smppi_batch* b, const C8A
   g.ob = dev_objective<R>(ob);
   g.grad_S = static_cast<const R*>(gS);
   g.grad_V = static_cast<R*>(gV);
-  const AdjScratch as = adjoint_scratch(b);
+  const AdjScratch as = adjoint_layout(ctx, b);
   g.nblk_max = as.nblk;
   g.seg_len = adj_seg_len(b->t_max);
   smppi_status st;
@@ -859,7 +867,7 @@ static smppi_status backward_t(smppi_ctx ctx, const smppi_batch* b, const smppi_
                                const uint32_t* iter, const void* gS, const smppi_objective* ob, void* gV,
                                hipStream_t s) {
   smppi_status st;
-  const AdjScratch as = adjoint_scratch(b);
+  const AdjScratch as = adjoint_layout(ctx, b);
   if ((st = need_scratch(ctx, as.pad_off + as.pad_bytes, (int)as.tickets, "smppi_rollout_backward")))
     return st;
   return backward_launch<R>(ctx, b, m, c, n, t, x0, V, iter, gS, ob, gV, as, ctx->scratch, ctx->tickets, s);

@@ -1,0 +1,65 @@
+"""smppi_reserve_batch covers every batch within the reserved bounds: the adjoints of a
+batch whose states would fit the scratch limit run, from checkpoints, on a ctx reserved
+for a larger batch beyond that limit."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2302_11719_amd import _lib as L
+from paper_2302_11719_amd import core
+from paper_2302_11719_amd import workloads as W
+
+from gpu_helpers import params, prep
+
+pytestmark = pytest.mark.gpu
+
+
+def _large(K, T):
+    p = W.config4(K=K, T=T, n_obs=8)
+    return prep([p], torch.float32)[0]
+
+
+@pytest.mark.parametrize("model", ["cartesian", "curvilinear"])
+def test_a_larger_reservation_covers_smaller_batches(model):
+    """The larger batch needs more than 1 GiB of stored states, the smaller does not (but
+    more than the checkpoints of the larger).  Tolerance as in
+    test_stored_and_checkpointed_adjoints_agree: both are FP32 sums of the same terms, a few
+    1e-6 from the FP64 gradient each; the curvilinear horizon is short, so that its chained
+    steps are as well conditioned."""
+    M, C = params(torch.float32)
+    K, K_large, T = (200000, 300000, 100) if model == "cartesian" else (800000, 900000, 30)
+    p = _large(K, T)
+    db = core.DeviceBatch([p])
+    g = torch.rand(p.K, generator=torch.Generator(device="cuda").manual_seed(2), device="cuda")
+    kappa, ds = W.curvature_table(p.track)
+    ct = core.CurvTrackArrays([(np.float32(kappa).astype(np.float64), float(np.float32(ds)))], [p.track.half_width])
+    x8 = torch.as_tensor(W.start_state_c8(vx=3.0), dtype=torch.float32, device="cuda")
+
+    def grad(reserve_k):
+        c = core.Context(0)
+        bounds = L.Batch.from_buffer_copy(bytes(db.batch))
+        bounds.k_max = reserve_k
+        assert L.lib().smppi_reserve_batch(c.h, ctypes.byref(bounds)) == 0
+        out = torch.full((2 * db.sum_T,), float("nan"), device="cuda")
+        ob, nz = L.objective_struct(W.OBJ_TOTAL), L.Noise(3, 0)
+        head = (c.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(M)))
+        tail = (core._p(db.V), core._p(db.iter), core._p(g), ctypes.byref(ob), core._p(out), core._stream())
+        if model == "cartesian":
+            st = L.lib().smppi_rollout_backward(*head, ctypes.byref(L.cost_struct(C)), ctypes.byref(nz),
+                                                ctypes.byref(db.track), core._p(db.x0), *tail)
+        else:
+            st = L.lib().smppi_rollout_backward_curvilinear(
+                *head, ctypes.byref(L.wheels_struct(W.wheels_f32())), ctypes.byref(L.cost_struct(C)), ctypes.byref(nz),
+                ctypes.byref(ct.track), core._p(x8), *tail)
+        assert st == 0, L.lib().smppi_last_error(c.h)
+        assert c.device_errors() == 0
+        c.close()
+        return out
+
+    print(f"{model}: K = {K} reserved for itself, then on a ctx reserved for K = {K_large}", flush=True)
+    own = grad(K)
+    large = grad(K_large)
+    assert torch.isfinite(own).all()
+    assert (large - own).norm() <= 5e-5 * own.norm()
