@@ -200,11 +200,10 @@ int smppi_abi_version(void);
  * bounds of `batch` (n_problems, k_max, t_max, dtype; its device arrays are not
  * read): the update's and the adjoint's per-workgroup partials
  * (dtype bytes x B x ceil(k_max / workgroup samples) x 2 x t_max), the adjoint's
- * stored states or checkpoints (see smppi_rollout_backward), 64 rows of
- * obstacles per problem (FP32, B x 64 x 16 bytes) and B ticket counters.
+ * stored states or checkpoints (see smppi_rollout_backward) and ticket counters.
  * Allocates (and synchronises) only when the ctx holds less; the scratch never
- * shrinks.  Call it before smppi_rollout (FP32 with obstacles), smppi_update
- * and smppi_rollout_backward, outside timed or captured regions. */
+ * shrinks.  Call it before smppi_update and the adjoints, outside timed or
+ * captured regions; the other plain calls need no scratch. */
 smppi_status smppi_reserve_batch(smppi_ctx ctx, const smppi_batch* batch);
 /* Synchronise the device, return (and clear) the OR of the input-bound errors
  * kernels detected on device data since the last call: 1 = some T_b outside
@@ -224,9 +223,7 @@ smppi_status smppi_device_errors(smppi_ctx ctx, uint32_t* flags);
  * x0: device [B][6] dtype.  V: device control sequences (layout above).
  * iter: device [B] uint32 iteration counters (noise counter word 3).
  * eps_out: NULL, or device [sum K][t_max][2] dtype receiving the effective
- *   noise u - v of every step (debug/test; rows beyond T_b untouched).
- * FP32 with obstacles: needs B * 64 * 16 bytes of ctx scratch (see
- * smppi_reserve_batch). */
+ *   noise u - v of every step (debug/test; rows beyond T_b untouched). */
 smppi_status smppi_rollout(smppi_ctx ctx, const smppi_batch* batch, const smppi_model* model,
                            const smppi_cost* cost, const smppi_noise* noise, const smppi_track* track,
                            const void* x0, const void* V, const uint32_t* iter, void* S, void* eps_out,

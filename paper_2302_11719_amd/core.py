@@ -147,7 +147,6 @@ def rollout(ctx: Context, db: DeviceBatch, model: dict, cost: dict, seed: int, n
     """smppi_rollout: per-sample modified costs S~ [sum K] (and effective noise if asked)."""
     S = db.new_S() if S is None else S
     eps = torch.zeros(db.sum_K * db.t_max * 2, dtype=db.dtype, device=db.device) if want_eps else None
-    ctx.reserve(db)
     st = L.lib().smppi_rollout(ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)),
                                ctypes.byref(L.cost_struct(cost)), ctypes.byref(_noise(seed, nominal)),
                                ctypes.byref(db.track), _p(db.x0 if x0 is None else x0), _p(db.V if V is None else V),

@@ -50,7 +50,7 @@ struct AdjScratch {
   size_t ck_off, ck_bytes;                   // checkpoints or stored rows: offset in the scratch, size
   size_t rows_bytes;                         // size of the stored rows of every step
   bool stored;                               // the adjoint stores every state (else checkpoints)
-  size_t pad_off, pad_bytes;                 // FP32 obstacle slots: offset, size
+  size_t bytes;                              // the whole layout
   int n_problems;
 };
 // Most memory the adjoint takes to store every state of every sample in the ctx

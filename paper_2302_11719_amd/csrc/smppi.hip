@@ -88,9 +88,7 @@ AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
                  (a.r == sizeof(float) ? adj_rows_bytes_per_wg<float>(b->t_max) : adj_rows_bytes_per_wg<double>(b->t_max));
   a.stored = a.rows_bytes <= max_rows;
   if (a.stored) a.ck_bytes = std::max(a.ck_bytes, a.rows_bytes);
-  // (64 rows of obstacles per problem are part of the documented reservation)
-  a.pad_off = (a.ck_off + a.ck_bytes + 255) & ~(size_t)255;
-  a.pad_bytes = b->dtype == SMPPI_F32 ? sizeof(float4) * (size_t)b->n_problems * kMaxObs : 0;
+  a.bytes = a.ck_off + a.ck_bytes;
   a.tickets = (size_t)b->n_problems * a.n_chunks;
   a.n_problems = b->n_problems;
   return a;
@@ -101,7 +99,7 @@ AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
 // its checkpoints cover those of every smaller batch).
 static AdjScratch adjoint_layout(smppi_ctx ctx, const smppi_batch* b) {
   const AdjScratch as = adjoint_scratch(b);
-  return as.pad_off + as.pad_bytes <= ctx->scratch_bytes ? as : adjoint_scratch(b, 0);
+  return as.bytes <= ctx->scratch_bytes ? as : adjoint_scratch(b, 0);
 }
 
 // Scratch of an update with spw samples per workgroup.
@@ -125,16 +123,10 @@ static int update_samples(const smppi_batch* b) {
 }
 
 // Scratch of the plain calls for a batch within these host bounds: the
-// update's per-workgroup partials [B][workgroups][2][t_max], the adjoint's
-// (adjoint_scratch) and, for FP32 rollouts with obstacles, the padded obstacle
-// slots [B][64].
+// update's per-workgroup partials [B][workgroups][2][t_max] or the adjoint's
+// (adjoint_scratch).
 size_t smppi::batch_scratch_bytes(const smppi_batch* b) {
-  const size_t B = (size_t)b->n_problems;
-  const size_t upd = update_bytes(b, update_samples(b));
-  const AdjScratch adj = adjoint_scratch(b);
-  const size_t bwd = adj.pad_off + adj.pad_bytes;
-  const size_t pad = b->dtype == SMPPI_F32 ? sizeof(float4) * B * kMaxObs : 0;
-  return std::max(upd, std::max(bwd, pad));
+  return std::max(update_bytes(b, update_samples(b)), adjoint_scratch(b).bytes);
 }
 
 smppi_status smppi::need_scratch(smppi_ctx ctx, size_t bytes, int tickets, const char* what) {
@@ -454,11 +446,6 @@ static smppi_status rollout_t(smppi_ctx ctx, const smppi_batch* b, const smppi_m
   a.V = static_cast<const R*>(V);
   a.S = static_cast<R*>(S);
   a.eps_out = static_cast<R*>(eps_out);
-  if (t->obs_max > 0 && b->k_max > 0 && sizeof(R) == sizeof(float)) {
-    // (the documented reservation; the kernels read the caller's rows)
-    const smppi_status st = need_scratch(ctx, sizeof(float4) * (size_t)b->n_problems * kMaxObs, 0, "smppi_rollout");
-    if (st) return st;
-  }
   if (t->obs_max > 0) return launch_rollout<R, kMaxObs>(ctx, b, a, s);
   return launch_rollout<R, 0>(ctx, b, a, s);
 }
@@ -611,7 +598,7 @@ static smppi_status backward_c8_t(smppi_ctx ctx, const smppi_batch* b, const C8A
   g.nblk_max = as.nblk;
   g.seg_len = adj_seg_len(b->t_max);
   smppi_status st;
-  if ((st = need_scratch(ctx, as.ck_off + as.ck_bytes, (int)as.tickets, "smppi_rollout_backward_curvilinear")))
+  if ((st = need_scratch(ctx, as.bytes, (int)as.tickets, "smppi_rollout_backward_curvilinear")))
     return st;
   g.part = static_cast<R*>(ctx->scratch);
   g.valid = adjoint_valid(as, ctx->scratch);
@@ -868,7 +855,7 @@ static smppi_status backward_t(smppi_ctx ctx, const smppi_batch* b, const smppi_
                                hipStream_t s) {
   smppi_status st;
   const AdjScratch as = adjoint_layout(ctx, b);
-  if ((st = need_scratch(ctx, as.pad_off + as.pad_bytes, (int)as.tickets, "smppi_rollout_backward")))
+  if ((st = need_scratch(ctx, as.bytes, (int)as.tickets, "smppi_rollout_backward")))
     return st;
   return backward_launch<R>(ctx, b, m, c, n, t, x0, V, iter, gS, ob, gV, as, ctx->scratch, ctx->tickets, s);
 }
@@ -964,8 +951,8 @@ extern "C" smppi_status smppi_rollout_backward_noalloc(smppi_ctx ctx, const smpp
   if (!ctx->noalloc) return fail(ctx, SMPPI_ERR_UNSUPPORTED, "no fixed scratch on device %d", ctx->device);
   // every state where that fits the fixed array too, else checkpoints
   AdjScratch as = adjoint_scratch(batch);
-  if (as.pad_off + as.pad_bytes > kNoAllocBytes - kNoAllocTicketBytes) as = adjoint_scratch(batch, 0);
-  const size_t part = as.pad_off + as.pad_bytes;
+  if (as.bytes > kNoAllocBytes - kNoAllocTicketBytes) as = adjoint_scratch(batch, 0);
+  const size_t part = as.bytes;
   if (as.tickets * sizeof(uint32_t) > kNoAllocTicketBytes || part > kNoAllocBytes - kNoAllocTicketBytes)
     return fail(ctx, SMPPI_ERR_SHAPE,
                 "smppi_rollout_backward_noalloc: the batch needs %zu ticket counters (B x ceil(2 t_max / 64); "

@@ -63,3 +63,25 @@ def test_a_larger_reservation_covers_smaller_batches(model):
     large = grad(K_large)
     assert torch.isfinite(own).all()
     assert (large - own).norm() <= 5e-5 * own.norm()
+
+
+def test_rollouts_need_no_scratch():
+    """FP32 rollouts read the caller's obstacle rows: nothing has to be reserved for them."""
+    M, C = params(torch.float32)
+    db = core.DeviceBatch([_large(300, 20)])
+
+    def costs(c):
+        S = torch.full((db.sum_K,), float("nan"), device="cuda")
+        st = L.lib().smppi_rollout(c.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(M)),
+                                   ctypes.byref(L.cost_struct(C)), ctypes.byref(L.Noise(3, 0)), ctypes.byref(db.track),
+                                   core._p(db.x0), core._p(db.V), core._p(db.iter), core._p(S), None, core._stream())
+        assert st == 0, L.lib().smppi_last_error(c.h)
+        assert c.device_errors() == 0
+        return S
+
+    c = core.Context(0)
+    print("rollout with obstacles before and after a reservation", flush=True)
+    S = costs(c)
+    c.reserve(db)
+    assert torch.equal(S, costs(c)) and torch.isfinite(S).all()
+    c.close()
