@@ -201,8 +201,9 @@ int smppi_abi_version(void);
  * read): the update's and the adjoint's per-workgroup partials
  * (dtype bytes x B x ceil(k_max / workgroup samples) x 2 x t_max), the adjoint's
  * stored states or checkpoints (see smppi_rollout_backward) and ticket counters.
- * Allocates (and synchronises) only when the ctx holds less; the scratch never
- * shrinks.  Call it before smppi_update and the adjoints, outside timed or
+ * Allocates (and synchronises) only when the ctx holds less, with at most 65 MiB of
+ * headroom; where the device has no room for the stored states, it reserves
+ * checkpoints.  The scratch never shrinks.  Call it before smppi_update and the adjoints, outside timed or
  * captured regions; the other plain calls need no scratch. */
 smppi_status smppi_reserve_batch(smppi_ctx ctx, const smppi_batch* batch);
 /* Synchronise the device, return (and clear) the OR of the input-bound errors

@@ -57,7 +57,6 @@ struct AdjScratch {
 // scratch (K = 65536, T = 100 in FP32: 265 MB); larger batches use checkpoints.
 constexpr size_t kMaxRows = (size_t)1 << 30;
 AdjScratch adjoint_scratch(const smppi_batch* b, size_t max_rows = kMaxRows);
-size_t batch_scratch_bytes(const smppi_batch* b);
 smppi_status need_scratch(smppi_ctx ctx, size_t bytes, int tickets, const char* what);
 smppi_status check_launch(smppi_ctx ctx, const char* what);
 smppi_status validate_batch(smppi_ctx ctx, const smppi_batch* b);

@@ -38,10 +38,14 @@ smppi_status smppi::hip_fail(smppi_ctx ctx, hipError_t e, const char* what) {
 
 smppi_status smppi::ensure_scratch(smppi_ctx ctx, size_t bytes) {
   if (bytes <= ctx->scratch_bytes) return SMPPI_OK;
-  size_t want = bytes + bytes / 2 + (1u << 20);
+  // (headroom, so that slowly growing batches do not reallocate each time)
+  size_t want = bytes + std::min(bytes / 2, (size_t)64 << 20) + (1u << 20);
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, want);
-  if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc(scratch)");
+  if (e != hipSuccess) {
+    (void)hipGetLastError();  // (the caller may do with less)
+    return hip_fail(ctx, e, "hipMalloc(scratch)");
+  }
   // In-flight work may still read the old buffer: keep it until destroy.
   if (ctx->scratch) ctx->retired.push_back(ctx->scratch);
   ctx->scratch = p;
@@ -125,8 +129,8 @@ static int update_samples(const smppi_batch* b) {
 // Scratch of the plain calls for a batch within these host bounds: the
 // update's per-workgroup partials [B][workgroups][2][t_max] or the adjoint's
 // (adjoint_scratch).
-size_t smppi::batch_scratch_bytes(const smppi_batch* b) {
-  return std::max(update_bytes(b, update_samples(b)), adjoint_scratch(b).bytes);
+static size_t batch_scratch_bytes(const smppi_batch* b, size_t max_rows = kMaxRows) {
+  return std::max(update_bytes(b, update_samples(b)), adjoint_scratch(b, max_rows).bytes);
 }
 
 smppi_status smppi::need_scratch(smppi_ctx ctx, size_t bytes, int tickets, const char* what) {
@@ -358,7 +362,10 @@ extern "C" smppi_status smppi_reserve_batch(smppi_ctx ctx, const smppi_batch* ba
   smppi_status st;
   if ((st = validate_batch(ctx, batch))) return st;
   (void)hipSetDevice(ctx->device);
-  if ((st = ensure_scratch(ctx, batch_scratch_bytes(batch)))) return st;
+  // without the memory to store every state, checkpoints (adjoint_layout)
+  if ((st = ensure_scratch(ctx, batch_scratch_bytes(batch))) &&
+      (st = ensure_scratch(ctx, batch_scratch_bytes(batch, 0))))
+    return st;
   return ensure_tickets(ctx, (int)std::max<size_t>(batch->n_problems, adjoint_scratch(batch).tickets));
 }
 

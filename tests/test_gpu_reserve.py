@@ -85,3 +85,39 @@ def test_rollouts_need_no_scratch():
     c.reserve(db)
     assert torch.equal(S, costs(c)) and torch.isfinite(S).all()
     c.close()
+
+
+def test_a_full_device_still_reserves_checkpoints():
+    """K = 262144, T = 100: 1.06 GB of stored states do not fit the 0.9 GB left on the
+    device, 0.2 GB of checkpoints do; the reservation succeeds and the adjoint runs."""
+    M, C = params(torch.float32)
+    db = core.DeviceBatch([_large(262144, 100)])
+    g = torch.zeros(db.sum_K, device="cuda")
+    g[::997] = 1.0
+    out = db.new_V()
+    c = core.Context(0)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    taken = []
+    try:
+        for _ in range(4):
+            left = torch.cuda.mem_get_info()[0]
+            if left > 950_000_000:
+                taken.append(torch.empty(left - 900_000_000, dtype=torch.uint8, device="cuda"))
+    except torch.cuda.OutOfMemoryError:
+        pytest.skip("the device's memory cannot be taken")
+    left = torch.cuda.mem_get_info()[0]
+    print(f"reserve with {left} bytes left", flush=True)
+    assert 600_000_000 < left < 1_000_000_000
+    try:
+        core.rollout_backward(c, db, M, C, 3, g, W.OBJ_TOTAL, out=out)
+        torch.cuda.synchronize()
+    finally:
+        taken.clear()
+        torch.cuda.empty_cache()
+    assert c.device_errors() == 0
+    own = core.Context(0)
+    ref = core.rollout_backward(own, db, M, C, 3, g, W.OBJ_TOTAL)  # from stored states
+    assert (out - ref).norm() <= 5e-5 * ref.norm()
+    c.close()
+    own.close()
