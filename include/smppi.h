@@ -242,9 +242,9 @@ smppi_status smppi_rollout_curvilinear(smppi_ctx ctx, const smppi_batch* batch, 
                                        const uint32_t* iter, void* S, void* eps_out, void* stream);
 
 /* Adjoint of smppi_rollout_curvilinear (as smppi_rollout_backward, with the
- * barrier read from e_y): grad_V = sum_m grad_S[m] dL_m/dV, states recomputed
- * from per-sample checkpoints.  Scratch as smppi_rollout_backward
- * (smppi_reserve_batch). */
+ * barrier read from e_y): grad_V = sum_m grad_S[m] dL_m/dV.  States are stored
+ * under the same rule, at 10 dtype bytes per sample and step, else recomputed from
+ * checkpoints (smppi_reserve_batch covers both models). */
 smppi_status smppi_rollout_backward_curvilinear(smppi_ctx ctx, const smppi_batch* batch, const smppi_model* model,
                                                 const smppi_wheels* wheels, const smppi_cost* cost,
                                                 const smppi_noise* noise, const smppi_curv_track* track,
@@ -291,10 +291,10 @@ smppi_status smppi_update(smppi_ctx ctx, const smppi_batch* batch, const smppi_m
  * (8 dtype bytes + 4)) and the ctx holds that much (it may have been reserved for a
  * larger batch, beyond that limit); otherwise states are recomputed from per-sample
  * checkpoints (every min(ceil(sqrt(t_max)), 12) steps, with each step's window
- * segment).  The two agree up to rounding.  Groups of 64 samples without upstream gradient are skipped.  Every 64
- * samples write a partial; a second small kernel adds them in a fixed order
- * (the result does not depend on scheduling).  grad_V has the
- * layout of V (dtype).  Gradients pass through the clip where it is inactive and
+ * segment).  The two agree up to rounding.  Groups of 64 samples without upstream
+ * gradient are skipped.  Every 64 samples write a partial; a second small kernel
+ * adds them in a fixed order (the result does not depend on scheduling).  grad_V
+ * has the layout of V (dtype).  Gradients pass through the clip where it is inactive and
  * through the hinge where it is active (one-sided at ties). */
 smppi_status smppi_rollout_backward(smppi_ctx ctx, const smppi_batch* batch, const smppi_model* model,
                                     const smppi_cost* cost, const smppi_noise* noise,

@@ -33,11 +33,12 @@ namespace smppi {
 
 // Stored rows of a workgroup: p_x, p_y, psi, v_x, v_y, omega of x_t and the two
 // unclipped controls of step t, [t_max + 1][8][64], then the window segment of
-// x_t, [t_max + 1][64] (curvilinear model: eight states and two controls).
+// x_t, [t_max + 1][64]; curvilinear model: the eight states and two controls,
+// [t_max + 1][10][64].
 constexpr int ADJ_ROW = 8, ADJ_ROW8 = 10;
 template <class R>
-__host__ __device__ inline size_t adj_rows_bytes_per_wg(int t_max) {
-  return (size_t)(t_max + 1) * WAVE * ADJ_ROW8 * sizeof(R);
+__host__ __device__ inline size_t adj_rows_bytes_per_wg(int t_max, bool curvilinear) {
+  return (size_t)(t_max + 1) * WAVE * (curvilinear ? ADJ_ROW8 * sizeof(R) : ADJ_ROW * sizeof(R) + sizeof(int));
 }
 
 constexpr int REV_D = 2;   // ring slots of the stage rows
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(RP_BLK) void k_backward_pipe(BackwardPipeArgs<R> ba
   const DevCost<R> C = cost_in_vgprs(a.C);
   const DevObjective<R> ob = a.ob;
   const State<R> x0 = load_state(a.p.x0 + 6 * (size_t)b);
-  unsigned char* wg = ba.rows + ((size_t)b * a.nblk_max + blockIdx.x) * adj_rows_bytes_per_wg<R>(a.p.t_max);
+  unsigned char* wg = ba.rows + ((size_t)b * a.nblk_max + blockIdx.x) * adj_rows_bytes_per_wg<R>(a.p.t_max, false);
   R* rows = reinterpret_cast<R*>(wg) + lane;
   int* segs = reinterpret_cast<int*>(wg + (size_t)(a.p.t_max + 1) * ADJ_ROW * WAVE * sizeof(R));
   // ---- forward: every state, unclipped control and window segment

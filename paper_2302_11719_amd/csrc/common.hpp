@@ -48,15 +48,16 @@ struct AdjScratch {
   int n_chunks;        // 64-output chunks of a control sequence (ceil(2 t_max / 64))
   size_t part_bytes, slice_bytes, tickets;  // slice_bytes includes the [B] validity flags at its end
   size_t ck_off, ck_bytes;                   // checkpoints or stored rows: offset in the scratch, size
-  size_t rows_bytes;                         // size of the stored rows of every step
+  size_t rows_bytes;                         // size of the stored rows of every step (adj_rows_bytes_per_wg)
   bool stored;                               // the adjoint stores every state (else checkpoints)
   size_t bytes;                              // the whole layout
   int n_problems;
 };
 // Most memory the adjoint takes to store every state of every sample in the ctx
-// scratch (K = 65536, T = 100 in FP32: 265 MB); larger batches use checkpoints.
+// scratch (K = 65536, T = 100 in FP32: 238 MB, curvilinear model 265 MB); larger
+// batches use checkpoints.
 constexpr size_t kMaxRows = (size_t)1 << 30;
-AdjScratch adjoint_scratch(const smppi_batch* b, size_t max_rows = kMaxRows);
+AdjScratch adjoint_scratch(const smppi_batch* b, bool curvilinear, size_t max_rows = kMaxRows);
 smppi_status need_scratch(smppi_ctx ctx, size_t bytes, int tickets, const char* what);
 smppi_status check_launch(smppi_ctx ctx, const char* what);
 smppi_status validate_batch(smppi_ctx ctx, const smppi_batch* b);

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(RP_BLK) void k_backward_c8_pipe(C8BackwardPipeArgs<
   const DevWheels<R> Wh = a.Wh;
   const DevObjective<R> ob = g.ob;
   const C8<R> x0 = load_c8(a.x0 + 8 * (size_t)b);
-  R* rows = reinterpret_cast<R*>(ba.rows + ((size_t)b * g.nblk_max + blockIdx.x) * adj_rows_bytes_per_wg<R>(a.t_max)) + lane;
+  R* rows = reinterpret_cast<R*>(ba.rows + ((size_t)b * g.nblk_max + blockIdx.x) * adj_rows_bytes_per_wg<R>(a.t_max, true)) + lane;
   // ---- forward
   if (w == 0) {
     pipe_noise<R, 64, C8P_D, 1>(M, C, Vs, T, a.seed, (uint32_t)m, (uint32_t)(a.pid_base + b), a.iter[b], a.nominal != 0,

@@ -70,7 +70,7 @@ smppi_status smppi::ensure_tickets(smppi_ctx ctx, int n) {
 // The adjoint's scratch for a batch: per-workgroup partials [B][nblk][2][t_max],
 // slice sums [B][ceil(nblk / SUM_SLICE)][2][t_max] (dtype) and ticket counters
 // [B][ceil(2 t_max / 64)] for the sum kernel.
-AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
+AdjScratch smppi::adjoint_scratch(const smppi_batch* b, bool curvilinear, size_t max_rows) {
   AdjScratch a;
   a.r = b->dtype == SMPPI_F32 ? sizeof(float) : sizeof(double);
   a.nblk = std::max(1, (std::max(0, b->k_max) + WAVE - 1) / WAVE);
@@ -89,7 +89,8 @@ AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
                                      : adj_ck_bytes_per_wg<double>(b->t_max, seg, 8, true));
   // every state instead of checkpoints where that takes little enough memory
   a.rows_bytes = (size_t)b->n_problems * a.nblk *
-                 (a.r == sizeof(float) ? adj_rows_bytes_per_wg<float>(b->t_max) : adj_rows_bytes_per_wg<double>(b->t_max));
+                 (a.r == sizeof(float) ? adj_rows_bytes_per_wg<float>(b->t_max, curvilinear)
+                                       : adj_rows_bytes_per_wg<double>(b->t_max, curvilinear));
   a.stored = a.rows_bytes <= max_rows;
   if (a.stored) a.ck_bytes = std::max(a.ck_bytes, a.rows_bytes);
   a.bytes = a.ck_off + a.ck_bytes;
@@ -101,9 +102,9 @@ AdjScratch smppi::adjoint_scratch(const smppi_batch* b, size_t max_rows) {
 // The layout a call uses: every state stored if the ctx holds that much, else
 // checkpoints (a ctx reserved for a batch beyond kMaxRows holds no stored states, but
 // its checkpoints cover those of every smaller batch).
-static AdjScratch adjoint_layout(smppi_ctx ctx, const smppi_batch* b) {
-  const AdjScratch as = adjoint_scratch(b);
-  return as.bytes <= ctx->scratch_bytes ? as : adjoint_scratch(b, 0);
+static AdjScratch adjoint_layout(smppi_ctx ctx, const smppi_batch* b, bool curvilinear) {
+  const AdjScratch as = adjoint_scratch(b, curvilinear);
+  return as.bytes <= ctx->scratch_bytes ? as : adjoint_scratch(b, curvilinear, 0);
 }
 
 // Scratch of an update with spw samples per workgroup.
@@ -127,10 +128,11 @@ static int update_samples(const smppi_batch* b) {
 }
 
 // Scratch of the plain calls for a batch within these host bounds: the
-// update's per-workgroup partials [B][workgroups][2][t_max] or the adjoint's
+// update's per-workgroup partials [B][workgroups][2][t_max] or either adjoint's
 // (adjoint_scratch).
 static size_t batch_scratch_bytes(const smppi_batch* b, size_t max_rows = kMaxRows) {
-  return std::max(update_bytes(b, update_samples(b)), adjoint_scratch(b, max_rows).bytes);
+  return std::max({update_bytes(b, update_samples(b)), adjoint_scratch(b, false, max_rows).bytes,
+                   adjoint_scratch(b, true, max_rows).bytes});
 }
 
 smppi_status smppi::need_scratch(smppi_ctx ctx, size_t bytes, int tickets, const char* what) {
@@ -366,7 +368,7 @@ extern "C" smppi_status smppi_reserve_batch(smppi_ctx ctx, const smppi_batch* ba
   if ((st = ensure_scratch(ctx, batch_scratch_bytes(batch))) &&
       (st = ensure_scratch(ctx, batch_scratch_bytes(batch, 0))))
     return st;
-  return ensure_tickets(ctx, (int)std::max<size_t>(batch->n_problems, adjoint_scratch(batch).tickets));
+  return ensure_tickets(ctx, (int)std::max<size_t>(batch->n_problems, adjoint_scratch(batch, false).tickets));
 }
 
 extern "C" smppi_status smppi_device_errors(smppi_ctx ctx, uint32_t* flags) {
@@ -601,7 +603,7 @@ static smppi_status backward_c8_t(smppi_ctx ctx, const smppi_batch* b, const C8A
   g.ob = dev_objective<R>(ob);
   g.grad_S = static_cast<const R*>(gS);
   g.grad_V = static_cast<R*>(gV);
-  const AdjScratch as = adjoint_layout(ctx, b);
+  const AdjScratch as = adjoint_layout(ctx, b, true);
   g.nblk_max = as.nblk;
   g.seg_len = adj_seg_len(b->t_max);
   smppi_status st;
@@ -861,7 +863,7 @@ static smppi_status backward_t(smppi_ctx ctx, const smppi_batch* b, const smppi_
                                const uint32_t* iter, const void* gS, const smppi_objective* ob, void* gV,
                                hipStream_t s) {
   smppi_status st;
-  const AdjScratch as = adjoint_layout(ctx, b);
+  const AdjScratch as = adjoint_layout(ctx, b, false);
   if ((st = need_scratch(ctx, as.bytes, (int)as.tickets, "smppi_rollout_backward")))
     return st;
   return backward_launch<R>(ctx, b, m, c, n, t, x0, V, iter, gS, ob, gV, as, ctx->scratch, ctx->tickets, s);
@@ -957,8 +959,8 @@ extern "C" smppi_status smppi_rollout_backward_noalloc(smppi_ctx ctx, const smpp
     return st;
   if (!ctx->noalloc) return fail(ctx, SMPPI_ERR_UNSUPPORTED, "no fixed scratch on device %d", ctx->device);
   // every state where that fits the fixed array too, else checkpoints
-  AdjScratch as = adjoint_scratch(batch);
-  if (as.bytes > kNoAllocBytes - kNoAllocTicketBytes) as = adjoint_scratch(batch, 0);
+  AdjScratch as = adjoint_scratch(batch, false);
+  if (as.bytes > kNoAllocBytes - kNoAllocTicketBytes) as = adjoint_scratch(batch, false, 0);
   const size_t part = as.bytes;
   if (as.tickets * sizeof(uint32_t) > kNoAllocTicketBytes || part > kNoAllocBytes - kNoAllocTicketBytes)
     return fail(ctx, SMPPI_ERR_SHAPE,

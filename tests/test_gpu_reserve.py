@@ -121,3 +121,17 @@ def test_a_full_device_still_reserves_checkpoints():
     assert (out - ref).norm() <= 5e-5 * ref.norm()
     c.close()
     own.close()
+
+
+def test_stored_states_take_their_documented_size():
+    """A state of the six-state adjoint takes 8 values and an index: K = 17280, T = 100 in
+    FP32 (63 MB) fits the fixed 64 MiB of the no-allocation entry point, which then gives
+    the bits of the reserved one."""
+    M, C = params(torch.float32)
+    db = core.DeviceBatch([_large(17280, 100)])
+    g = torch.rand(db.sum_K, generator=torch.Generator(device="cuda").manual_seed(4), device="cuda")
+    c = core.Context(0)
+    a = core.rollout_backward(c, db, M, C, 3, g, W.OBJ_TOTAL)
+    b = core.rollout_backward(c, db, M, C, 3, g, W.OBJ_TOTAL, noalloc=True)
+    assert torch.equal(a, b) and c.device_errors() == 0
+    c.close()
