@@ -421,7 +421,8 @@ smppi_status smppi_plan_info(smppi_plan plan, int32_t* grid, int32_t* block, int
  * VALU issue, ragged batches by the tail of the tile queue), so the tuner
  * times candidates on the caller's own batch. */
 typedef struct {
-  int32_t pipeline;  /* 1: latency mode (block, tile ignored); -1: tile mode */
+  int32_t pipeline;  /* 1: latency mode (block, tile ignored); -1: tile mode; 0 with
+                        block, tile and grid 0: what a plan picks by itself */
   int32_t block;     /* tile mode: 64, 128, 256 or 512 */
   int32_t tile;      /* tile mode: samples per tile, a multiple of block */
   int32_t grid;      /* persistent workgroups; 0 = from occupancy */
@@ -442,9 +443,10 @@ int32_t smppi_autotune_candidates(int32_t n_cu, smppi_tune_entry* out, int32_t c
 smppi_status smppi_autotune_key(int32_t n_problems, const int64_t* k_off_host, const int32_t* t_off_host,
                                 int32_t has_obstacles, int32_t n_cu, char* out, int32_t cap);
 
-/* Times each candidate (cands [n_cands] host, or the default set when cands is
- * NULL) on this batch: a plan with the shield, execute and graph off, warmup +
- * reps profiled launches, the median of the fused kernel's own duration.
+/* Times each candidate (cands [n_cands] host; when cands is NULL the automatic
+ * configuration, all fields 0, and the default set) on this batch: a plan with the shield, execute and graph off, warmup +
+ * reps profiled launches, the median of the fused kernel's own duration (from the
+ * start of the rollout kernel where the automatic configuration has one).
  * table (host, table_cap entries, may be NULL) receives the candidates, the
  * timed ones fastest first, then those that cannot be built for this batch
  * (kernel_ms = -1); *n_table their count (entries beyond table_cap are
@@ -453,7 +455,7 @@ smppi_status smppi_autotune_key(int32_t n_problems, const int64_t* k_off_host, c
  * overwritten.  With cache_path (host string, may be NULL): a result stored
  * under the batch's shape key is returned without timing, *cached = 1 (table
  * then holds that one entry), unless force; a new result replaces the key's line
- * of the file (text, one "key pipeline block tile grid kernel_ms" line per key,
+ * of the file (text, one "2/key pipeline block tile grid kernel_ms" line per key,
  * written to a temporary file in the same directory and renamed; the directory
  * must exist).  Not for hot loops: it creates plans (device allocations),
  * synchronises the device and does file I/O.  Errors: as smppi_plan_create for

@@ -1,6 +1,7 @@
 """Launch-geometry autotuner for the batched plan.
 
-The fused kernel of a plan has four knobs: the four-wave latency mode
+A plan picks its configuration by itself; that choice (all knobs 0) is timed against the
+fused kernel's four knobs: the four-wave latency mode
 (``pipeline``), the workgroup size (``block``: 64, 128, 256, 512), the samples
 per tile (``tile`` = block x samples-per-thread, 1, 2 or 4) and the number of
 persistent workgroups (``grid``; 0 = the occupancy limit).  Which is fastest
@@ -95,21 +96,23 @@ def tune(ctx: core.Context, db: core.DeviceBatch, model: dict, cost: dict, seed:
     stats = torch.empty(4 * db.B, dtype=db.dtype, device=db.device)
     bufs = L.PlanBuffers(db.x0.data_ptr(), db.V.data_ptr(), db.iter.data_ptr(), S.data_ptr(), V_plus.data_ptr(),
                          stats.data_ptr(), None)
-    cl = list(cands) if cands is not None else candidates(n_cu)
-    carr = (L.TuneEntry * len(cl))(*[_entry(c) for c in cl])
-    table = (L.TuneEntry * len(cl))()
+    # without candidates the library times its own set, the automatic configuration first
+    carr = (L.TuneEntry * len(cands))(*[_entry(c) for c in cands]) if cands is not None else None
+    n_cands = len(cands) if cands is not None else 0
+    n_rows = n_cands if cands is not None else 1 + len(candidates(n_cu))
+    table = (L.TuneEntry * n_rows)()
     best, cached, n_table = L.TuneEntry(), ctypes.c_int32(0), ctypes.c_int32(0)
     torch.cuda.synchronize()
     st = L.lib().smppi_autotune(ctx.h, ctypes.byref(db.batch), ctypes.byref(L.model_struct(model)),
                                 ctypes.byref(L.cost_struct(cost)), ctypes.byref(core._noise(seed, False)),
-                                ctypes.byref(db.track), float(lam), ctypes.byref(bufs), carr, len(cl), int(reps),
+                                ctypes.byref(db.track), float(lam), ctypes.byref(bufs), carr, n_cands, int(reps),
                                 int(warmup), cache.encode() if cache else None, 1 if force else 0, ctypes.byref(best),
-                                ctypes.byref(cached), table, len(cl), ctypes.byref(n_table),
-                                ctypes.c_void_p(core._stream()))
+                                ctypes.byref(cached), table, n_rows, ctypes.byref(n_table),
+                                core._stream())
     ctx.check(st, "smppi_autotune")
     steps = int(sum(k * t for k, t in zip(db.K, db.T)))
     rows = []
-    for e in table[: min(n_table.value, len(cl))]:
+    for e in table[: min(n_table.value, n_rows)]:
         ms = float(e.kernel_ms)
         rows.append(dict(_dict(e), kernel_ms=ms, rollout_steps_per_s=steps / (ms * 1e-3) if ms > 0 else None))
     return TuneResult(key, _dict(best), float(best.kernel_ms), rows, cached=bool(cached.value))

@@ -1242,7 +1242,8 @@ extern "C" smppi_status smppi_autotune(smppi_ctx ctx, const smppi_batch* batch, 
   char keybuf[256];
   if ((st = smppi_autotune_key(B, koff.data(), toff.data(), track->obs_max > 0, ctx->n_cu, keybuf, sizeof keybuf)))
     return fail(ctx, st, "batch shape key");
-  const std::string key(keybuf);
+  // (entries without the prefix date from before the automatic configuration was timed)
+  const std::string key = std::string("2/") + keybuf;
   if (cache_path && !force) {
     smppi_tune_entry hit{};
     if (cache_lookup(cache_path, key, &hit)) {
@@ -1253,8 +1254,16 @@ extern "C" smppi_status smppi_autotune(smppi_ctx ctx, const smppi_batch* batch, 
       return SMPPI_OK;
     }
   }
-  const std::vector<smppi_tune_entry> cand =
-      cands ? std::vector<smppi_tune_entry>(cands, cands + n_cands) : default_candidates(ctx->n_cu);
+  // The default set, and before it the automatic configuration (all fields 0): the only
+  // one that runs its rollouts as a step pipeline of their own (plan_rollout_pays).
+  const smppi_tune_entry automatic{0, 0, 0, 0, 0.f};
+  std::vector<smppi_tune_entry> cand;
+  if (cands) {
+    cand.assign(cands, cands + n_cands);
+  } else {
+    cand = default_candidates(ctx->n_cu);
+    cand.insert(cand.begin(), automatic);
+  }
   smppi_plan_opts o{};
   o.lambda = lambda;
   o.use_graph = 0;
@@ -1264,7 +1273,8 @@ extern "C" smppi_status smppi_autotune(smppi_ctx ctx, const smppi_batch* batch, 
   std::vector<smppi_tune_entry> done, skipped;
   std::vector<float> ms;
   for (smppi_tune_entry c : cand) {
-    o.pipeline = c.pipeline == 1 ? 1 : -1;
+    const bool is_auto = c.pipeline == 0 && c.block == 0 && c.tile == 0 && c.grid == 0;
+    o.pipeline = is_auto ? 0 : (c.pipeline == 1 ? 1 : -1);
     o.block = c.pipeline == 1 ? 0 : c.block;
     o.tile = c.pipeline == 1 ? 0 : c.tile;
     o.grid = c.grid;
