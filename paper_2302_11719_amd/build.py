@@ -12,7 +12,6 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsmppi.so")
 SOURCES = ["smppi.hip", "plan.hip"]
-HEADERS = ["device.hpp", "kernels.hpp", "curv8.hpp", "pipe.hpp", "common.hpp"]
 ARCH = os.environ.get("SMPPI_ARCH", "gfx950")
 
 FLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wall", "-Wno-unused-variable",
