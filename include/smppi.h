@@ -354,7 +354,8 @@ typedef struct {
                                 batch has at least 16 block samples per CU, else block */
   int32_t grid;              /* persistent workgroups; 0 = chosen from occupancy */
   int32_t use_graph;         /* nonzero: capture into a hipGraph at creation when a launch
-                                has more than one kernel (one kernel is launched directly) */
+                                has a kernel besides rollouts, weights and update (these
+                                alone, one or two kernels, are launched directly) */
   int32_t pipeline;          /* 1: latency mode (64-sample tiles, four specialised waves
                                 pipelining noise, dynamics and cost); -1: off; 0: on when
                                 the batch has at most 2*64 samples per compute unit and
@@ -395,7 +396,7 @@ smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batch, const sm
                                const smppi_plan_opts* opts, const smppi_plan_buffers* bufs,
                                smppi_plan* out);
 /* One MPPI iteration of every problem: rollout, weights and update fused in one
- * persistent launch, then (optionally) the shield and the execute/warm start.
+ * persistent launch (the rollouts in a launch before it where that is faster), then (optionally) the shield and the execute/warm start.
  * The obstacles are read at every launch, so they may move in between. */
 smppi_status smppi_plan_launch(smppi_plan plan, void* stream);
 void smppi_plan_destroy(smppi_plan plan);

@@ -11,9 +11,10 @@
 // workgroup then runs it on the problem (Algorithm 1 or L-BFGS) and, when the
 // plan executes, the plant step and warm start, all in the same launch (a
 // separate shield kernel when the workgroup has fewer than three waves or its
-// LDS does not fit; a separate execute kernel without the shield).  A launch
-// of several kernels (empty problems, separate shield or execute) is captured once into a HIP graph; a single kernel is launched
-// directly.
+// LDS does not fit; a separate execute kernel without the shield).  Where it is
+// faster the rollouts are a kernel of their own before k_fused (a split plan).  With
+// use_graph a launch that also has empty problems, a separate shield or a separate
+// execute is captured once into a HIP graph; else the kernels are launched directly.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -998,7 +999,9 @@ extern "C" smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batc
   a.queue = p->counters;
   a.tickets = p->counters + 1;
   a.exits = p->counters + 1 + B;
-  p->lds = (int)stage_lds_bytes<float>(track->poly_max, batch->t_max, obs_slots(track));
+  // (with the rollouts given, the controls are all that the kernel stages)
+  p->lds = (int)(given ? sizeof(float) * 2 * (size_t)batch->t_max
+                       : stage_lds_bytes<float>(track->poly_max, batch->t_max, obs_slots(track)));
   hipFuncAttributes fattr{};
   if ((e = hipFuncGetAttributes(&fattr, reinterpret_cast<const void*>(fn))) != hipSuccess)
     return bail(hip_fail(ctx, e, "hipFuncGetAttributes"));
@@ -1041,8 +1044,9 @@ extern "C" smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batc
   int grid = opts->grid > 0 ? opts->grid : ctx->n_cu * per_cu;
   grid = std::max(1, std::min(grid, std::max(1, n_tiles)));
   p->grid = grid;
-  // A graph only pays when the launch has several kernels; a single kernel is
-  // launched directly (measured: the one-node graph adds about 4 us per launch).
+  // A single kernel is launched directly (the one-node graph adds about 4 us per launch),
+  // and so is the pair of a split plan (as a graph K = 65536, T = 100: 97 -> 101 us,
+  // K = 1000, T = 20: 27.5 -> 31.2).
   const int n_kernels = (any_empty ? 1 : 0) + (n_tiles > 0 ? 1 : 0) + (opts->repair && !p->fused_shield ? 1 : 0) +
                         (opts->execute && !opts->repair ? 1 : 0);
   if (opts->use_graph && n_kernels > 1) {
