@@ -462,10 +462,12 @@ struct UpdateArgs {
 constexpr int UPD_BLOCK = 256;
 constexpr int UPD_TCHUNK = 64;
 
-// The ticket protocol, at device scope: every partial the last ticket holder reads is
-// written with store_agent (a write-through store, complete at the level the XCDs share
-// when the wave's store counter drains), ticket_release waits for the wave's stores, and
-// the barrier after it puts every wave's wait before the ticket increment.  (A release
+// The ticket protocol, at device scope.  RULE: with THROUGH, whatever the last ticket
+// holder reads must have been written with store_agent; a plain store before
+// ticket_release<true> is not ordered, since that is a wait and no release.  store_agent
+// is a write-through store, complete at the level the XCDs share when the wave's store
+// counter drains; ticket_release waits for the wave's stores, and the barrier after it
+// puts every wave's wait before the ticket increment.  (A release
 // fence after plain stores writes back the whole L2 for each workgroup: 12 of the 26 us
 // of a launch of 256 tiles that finish together, against 2.4 us.  THROUGH = false keeps
 // plain stores and the fence: the tiles of a long launch finish one by one, where it
