@@ -72,6 +72,12 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 }
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
 // 32x32 -> 64-bit products with a Weyl-sequence key schedule.
+// X3: three-way xors in one instruction (truth table 0x96) from the fourth round on;
+// before it part of the operands is uniform and stays on the scalar unit (13 VALU
+// instructions fewer per call; ragged batch of 512 problems 890 -> 880 us).  The plain
+// FP32 rollout without obstacles is slower with them at every size (T = 50, K = 70000
+// 61.5 -> 63.7 us, K = 524288 184.6 -> 188.6) and takes two-way xors.
+template <bool X3 = true>
 __device__ __forceinline__ void philox4x32_10(uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3,
                                               uint32_t k0, uint32_t k1) {
 #pragma unroll
@@ -81,11 +87,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t& c0, uint32_t& c1, uint32
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
     const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
     const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-    // three-way xor in one instruction (truth table 0x96) from the fourth round
-    // on; before it part of the operands is uniform and stays on the scalar unit (13
-    // VALU instructions fewer per call; ragged batch of 512 problems 890 -> 880 us)
-    const uint32_t n0 = r < 3 ? hi1 ^ c1 ^ k0 : xor3(hi1, c1, k0);
-    const uint32_t n2 = r < 4 ? hi0 ^ c3 ^ k1 : xor3(hi0, c3, k1);
+    const uint32_t n0 = !X3 || r < 3 ? hi1 ^ c1 ^ k0 : xor3(hi1, c1, k0);
+    const uint32_t n2 = !X3 || r < 4 ? hi0 ^ c3 ^ k1 : xor3(hi0, c3, k1);
     c0 = n0;
     c1 = lo1;
     c2 = n2;
@@ -116,24 +119,24 @@ __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, double& z0, d
 
 // Four standard normals for steps 2j and 2j+1 of sample m: counter
 // (j, m, pid, it), key (seed, 0).
-template <class R>
+template <class R, bool X3 = true>
 __device__ __forceinline__ void normals4(uint32_t seed, uint32_t j, uint32_t m, uint32_t pid, uint32_t it,
                                          R z[4]) {
   uint32_t c0 = j, c1 = m, c2 = pid, c3 = it;
-  philox4x32_10(c0, c1, c2, c3, seed, 0u);
+  philox4x32_10<X3>(c0, c1, c2, c3, seed, 0u);
   box_muller(c0, c1, z[0], z[1]);
   box_muller(c2, c3, z[2], z[3]);
 }
 
 // Per-step noise of one sample: one Philox call covers the pair of steps
 // (2j, 2j+1).  gen(t) regenerates the pair containing t; get(t) reads it.
-template <class R>
+template <class R, bool X3 = true>
 struct NoiseStream {
   uint32_t seed, m, pid, it;
   bool nominal;
   R z[4];
   __device__ __forceinline__ void gen(int t) {
-    if (!nominal) normals4<R>(seed, (uint32_t)(t >> 1), m, pid, it, z);
+    if (!nominal) normals4<R, X3>(seed, (uint32_t)(t >> 1), m, pid, it, z);
   }
   __device__ __forceinline__ void get(int t, R sig0, R sig1, R& e0, R& e1) const {
     if (nominal) {
@@ -741,9 +744,9 @@ __device__ __forceinline__ DevCost<R> cost_in_vgprs(const DevCost<R>& C) {
 //   S~ = sum_{t<T} [q(x_t) + lambda_u v_t^T Sigma^-1 u_t] + phi_w q(x_T) + sum_{t=0}^{T} C_cbf(z_t).
 // V is [2][T] (steer row, throttle row), read from LDS or global.  Obstacles
 // come from `os` (LdsObstacles, or WaveObstacles: FP32, the whole wave active).
-template <class R, int NOBS, class OS>
+template <class R, int NOBS, class NS, class OS>
 __device__ R rollout_sample(const DevModel<R>& Mg, const DevCost<R>& Cg, const TrackView<R>& tr, const State<R>& x0,
-                            const R* __restrict__ V, int T, NoiseStream<R>& ns, R* eps_out, const OS& os) {
+                            const R* __restrict__ V, int T, NS& ns, R* eps_out, const OS& os) {
   // (with obstacles: the kernels run one wave per SIMD, so the VGPRs are free;
   // without, the copies would cost occupancy)
   DevModel<R> Mv;
@@ -863,9 +866,9 @@ __device__ R rollout_sample(const DevModel<R>& Mg, const DevCost<R>& Cg, const T
   return S;
 }
 
-template <class R, int NOBS>
+template <class R, int NOBS, class NS>
 __device__ R rollout_sample(const DevModel<R>& M, const DevCost<R>& C, const TrackView<R>& tr, const State<R>& x0,
-                            const R* __restrict__ V, int T, NoiseStream<R>& ns, R* eps_out) {
+                            const R* __restrict__ V, int T, NS& ns, R* eps_out) {
   return rollout_sample<R, NOBS>(M, C, tr, x0, V, T, ns, eps_out, LdsObstacles<R>{&tr});
 }
 
