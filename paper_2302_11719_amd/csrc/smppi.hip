@@ -561,10 +561,11 @@ static smppi_status rollout_c8_t(smppi_ctx ctx, const smppi_batch* b, const C8Ar
   // Few samples: the step pipeline (same bits), up to six workgroups of 64 samples
   // per compute unit in FP32 and two in FP64 (K = 4096, T = 50: 51.7 -> 32.9 us,
   // FP64 121 -> 71.9; FP32 K = 98304: 69.3 -> 61.7, at 131072 70.2 against 83.5;
-  // FP64 T = 100, K = 65536: 248 against 314).
+  // FP64 T = 100, K = 65536: 248 against 314), from three steps on (K = 4096: T = 2
+  // 4.9 against 5.3 us, T = 3 6.0 against 5.9).
   const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + WAVE - 1) / WAVE);
   const size_t lds_p = lds + sizeof(C8PipeLds<R>);
-  if (n64 <= (sizeof(R) == 4 ? 6 : 2) * ctx->n_cu && lds_p <= (size_t)ctx->max_lds) {
+  if (a.t_max >= 3 && n64 <= (sizeof(R) == 4 ? 6 : 2) * ctx->n_cu && lds_p <= (size_t)ctx->max_lds) {
     hipLaunchKernelGGL((k_rollout_c8_pipe<R>), dim3((b->k_max + WAVE - 1) / WAVE, b->n_problems), dim3(C8P_BLK), lds_p,
                        s, a, static_cast<R*>(S), static_cast<R*>(eps_out));
     return check_launch(ctx, "k_rollout_c8_pipe");
