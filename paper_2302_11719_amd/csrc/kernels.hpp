@@ -1711,6 +1711,25 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
       }
       if (act && (ob.w_sq != R(0) || (ob.w_lin != R(0) && t < ob.n_lin))) last = t;
     };
+    // The fourth wave.  Its branch is laid out behind the others' code: between them it
+    // cost an idle shield 0.3 to 0.5 us, also where it has nothing to do (inside a plan of
+    // K = 1000, T = 6: 23.5 -> 23.0 us), and which order does it differs by type.
+    auto rows_ahead = [&]() {
+      // Jacobian rows of REP_AHEAD steps (six per step on the lanes) once the
+      // pose of the last of them is there (its stage velocities came before)
+      const int k = lane / 6;
+      int seenv = 0, seenp = 0;
+      for (int t0 = 0; t0 < t_ahead; t0 += REP_AHEAD) {
+        wave_wait(flg, t0 + REP_AHEAD - 1, seenv, a.p.err);
+        wave_wait(flg + 1, t0 + REP_AHEAD - 2, seenp, a.p.err);
+        const int t = t0 + k;
+        int i = lane % 6;
+        asm volatile("" : "+v"(i));  // (same basic block as its uses: see shield_jac_row)
+        if (k < REP_AHEAD)  // (the states' velocities are still in the stages' rows)
+          shield_jac_row(M, Vs, T, t, i, xs + 6 * t, vst + 12 * (size_t)t, 4,
+                         wpar + (size_t)REP_PAR_PER_STEP * t + 8 * i);
+      }
+    };
     if constexpr (VG) {
       // (kernels with one workgroup per compute unit: the shield kernel, the
       // latency-mode plan) step by step through the LDS step counters
@@ -1798,23 +1817,8 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
           wave_publish(flg + 1, t + 1);
           asm volatile("" : "+v"(x.px), "+v"(x.py), "+v"(x.psi)::"memory");
         }
-      } else if (__builtin_expect(w == 3 && t_ahead > 0, 0)) {
-        // (laid out behind the rest: between the other waves' code it cost an idle shield
-        // inside a small plan 0.4 us; K = 1000, T = 6: 23.5 -> 23.0 us)
-        // Jacobian rows of REP_AHEAD steps (six per step on the lanes) once the
-        // pose of the last of them is there (its stage velocities came before)
-        const int k = lane / 6;
-        int seenv = 0, seenp = 0;
-        for (int t0 = 0; t0 < t_ahead; t0 += REP_AHEAD) {
-          wave_wait(flg, t0 + REP_AHEAD - 1, seenv, a.p.err);
-          wave_wait(flg + 1, t0 + REP_AHEAD - 2, seenp, a.p.err);
-          const int t = t0 + k;
-          int i = lane % 6;
-          asm volatile("" : "+v"(i));  // (same basic block as its uses: see shield_jac_row)
-          if (k < REP_AHEAD)  // (the states' velocities are still in the stages' rows)
-            shield_jac_row(M, Vs, T, t, i, xs + 6 * t, vst + 12 * (size_t)t, 4,
-                           wpar + (size_t)REP_PAR_PER_STEP * t + 8 * i);
-        }
+      } else if (sizeof(R) == 4 && __builtin_expect(w == 3 && t_ahead > 0, 0)) {
+        rows_ahead();
       } else if (w == 1) {
         // window wave: e_y^2, obstacle barriers and activity of each new position.
         // A chunk's segment indices collect on lanes 0 .. REP_C-1 and are stored
@@ -1853,6 +1857,8 @@ __device__ void repair_problem(const RepairArgs<R>& a, int b, const ProblemDims&
             e2s[t0 + 1 + lane] = ec;
           }
         }
+      } else if (sizeof(R) == 8 && __builtin_expect(w == 3 && t_ahead > 0, 0)) {
+        rows_ahead();
       }
       __syncthreads();
       // velocities of x_1 .. x_{T-1}: the first stage of the next step's row
