@@ -718,6 +718,12 @@ FusedFn pick_pipe(bool fuse) {
 
 }  // namespace
 
+// The offsets of a one-problem plan as read at its creation (k_fused has them as d1).
+struct OneProblemOffsets {
+  int64_t k[2];
+  int32_t t[2], poly[2];
+};
+
 struct smppi_plan_s {
   smppi_ctx ctx = nullptr;
   smppi_batch batch{};
@@ -738,6 +744,7 @@ struct smppi_plan_s {
   int32_t* tile_off = nullptr;
   float* part = nullptr;
   uint32_t* counters = nullptr;  // [0] queue, [1..B] tickets, [B+1] exits
+  OneProblemOffsets* offsets = nullptr;  // one-problem split plans: what the rollout launch reads
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -783,6 +790,11 @@ static smppi_status plan_enqueue(smppi_plan p, hipStream_t s, bool profiled = fa
     if (p->given) {
       RolloutArgs<float> ra{};
       ra.p = p->fa.p;
+      if (p->offsets) {
+        ra.p.k_off = p->offsets->k;
+        ra.p.t_off = p->offsets->t;
+        if (ra.p.poly_off) ra.p.poly_off = p->offsets->poly;
+      }
       ra.M = p->fa.M;
       ra.C = p->fa.C;
       ra.V = p->fa.V;
@@ -830,6 +842,7 @@ extern "C" void smppi_plan_destroy(smppi_plan p) {
   if (p->tile_off) (void)hipFree(p->tile_off);
   if (p->part) (void)hipFree(p->part);
   if (p->counters) (void)hipFree(p->counters);
+  if (p->offsets) (void)hipFree(p->offsets);
   delete p;
 }
 
@@ -991,6 +1004,12 @@ extern "C" smppi_status smppi_plan_create(smppi_ctx ctx, const smppi_batch* batc
                     d.np >= 0 && d.np <= track->poly_max && !(d.np > 0 && 2 * track->window + 1 > d.np) &&
                     d.no >= 0 && d.no <= track->obs_max;
     a.one = ok ? 1 : 0;
+    if (ok && given) {
+      const OneProblemOffsets o{{koff[0], koff[1]}, {toff[0], toff[1]}, {po[0], po[1]}};
+      if ((e = hipMalloc(&p->offsets, sizeof(o))) != hipSuccess ||
+          (e = hipMemcpy(p->offsets, &o, sizeof(o), hipMemcpyHostToDevice)) != hipSuccess)
+        return bail(hip_fail(ctx, e, "hipMalloc(offsets)"));
+    }
   }
   a.tile_off = p->tile_off;
   a.n_tiles = n_tiles;
