@@ -286,7 +286,7 @@ __device__ __forceinline__ R penalty_grad_c8(const DevCost<R>& C, const DevObjec
 // (23)-(25)), as rollout_sample with the barrier read from e_y.
 template <class R>
 __device__ R rollout_sample_c8(const DevModel<R>& M, const DevWheels<R>& Wh, const DevCost<R>& C,
-                               const CurvView<R>& cv, C8<R> x, const R* __restrict__ V, int T, NoiseStream<R>& ns,
+                               const CurvView<R>& cv, C8<R> x, const R* __restrict__ V, int T, NoiseStream<R, false>& ns,
                                R* eps_out) {
   R h0 = cv.w2 - x.ey * x.ey;
   bool outside = h0 < R(0);
@@ -405,8 +405,8 @@ __host__ __device__ inline size_t c8_stage_bytes(int n_max, int t_max) {
 }
 
 template <class R>
-__device__ __forceinline__ NoiseStream<R> c8_noise(const C8Args<R>& a, int b, int m) {
-  NoiseStream<R> ns;
+__device__ __forceinline__ NoiseStream<R, false> c8_noise(const C8Args<R>& a, int b, int m) {
+  NoiseStream<R, false> ns;
   ns.seed = a.seed;
   ns.m = (uint32_t)m;
   ns.pid = (uint32_t)(a.pid_base + b);
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(256) void k_rollout_c8(C8Args<R> a, R* S, R* eps_ou
   __syncthreads();
   const int m = m_base + threadIdx.x;
   if (m >= d.K) return;
-  NoiseStream<R> ns = c8_noise(a, b, m);
+  NoiseStream<R, false> ns = c8_noise(a, b, m);
   R* eo = eps_out ? eps_out + ((size_t)(d.k0 + m)) * a.t_max * 2 : nullptr;
   S[d.k0 + m] = rollout_sample_c8(a.M, a.Wh, a.C, cv, load_c8(a.x0 + 8 * (size_t)b), Vs, d.T, ns, eo);
 }
@@ -441,7 +441,7 @@ __global__ __launch_bounds__(256) void k_rollout_c8(C8Args<R> a, R* S, R* eps_ou
 template <class R, class Sink>
 __device__ void adjoint_lane_c8(const DevModel<R>& M, const DevWheels<R>& Wh, const DevCost<R>& C,
                                 const DevObjective<R>& ob, const CurvView<R>& cv, const C8<R>& x0, const R* V, int T,
-                                NoiseStream<R>& ns, R* ck, R* sx, int seg_len, int lane, Sink& sink) {
+                                NoiseStream<R, false>& ns, R* ck, R* sx, int seg_len, int lane, Sink& sink) {
   C8<R> x = x0;
   for (int t = 0; t < T; ++t) {
     if (t % seg_len == 0) store_c8_lane(ck + (size_t)(t / seg_len) * 8 * WAVE, lane, x);
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(WAVE) void k_backward_c8(C8BackwardArgs<R> g) {
   __syncthreads();
   const int lane = threadIdx.x;
   const int m = blockIdx.x * WAVE + lane;
-  NoiseStream<R> ns = c8_noise(a, b, m);
+  NoiseStream<R, false> ns = c8_noise(a, b, m);
   ReduceSink<R> sink;
   sink.g = (m < d.K) ? g.grad_S[d.k0 + m] : R(0);
   sink.gp = g.part + ((size_t)b * g.nblk_max + blockIdx.x) * 2 * a.t_max;

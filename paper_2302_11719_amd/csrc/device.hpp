@@ -75,8 +75,10 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 // X3: three-way xors in one instruction (truth table 0x96) from the fourth round on;
 // before it part of the operands is uniform and stays on the scalar unit (13 VALU
 // instructions fewer per call; ragged batch of 512 problems 890 -> 880 us).  The plain
-// FP32 rollout without obstacles is slower with them at every size (T = 50, K = 70000
-// 61.5 -> 63.7 us, K = 524288 184.6 -> 188.6) and takes two-way xors.
+// rollout without obstacles is slower with them (T = 50, FP32: K = 70000 61.5 -> 63.7 us,
+// K = 524288 184.6 -> 188.6; FP64, 256 x K = 256, T = 20 57.2 -> 58.2), the curvilinear
+// one with a long table too (8000 points, FP64, K = 32768, T = 50: 126 -> 129): these
+// take two-way xors.
 template <bool X3 = true>
 __device__ __forceinline__ void philox4x32_10(uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3,
                                               uint32_t k0, uint32_t k1) {

@@ -325,7 +325,7 @@ __global__ __launch_bounds__(256) void k_rollout(RolloutArgs<R> a) {
   if (WV ? (m - (int)(threadIdx.x % WAVE) >= d.K) : (m >= d.K)) return;
   const bool own = m < d.K;
   const int mr = own ? m : d.K - 1;
-  NoiseStream<R, (NOBS > 0 || sizeof(R) == 8)> ns;
+  NoiseStream<R, (NOBS > 0)> ns;
   ns.seed = a.p.seed;
   ns.m = (uint32_t)mr;
   ns.pid = (uint32_t)(a.p.pid_base + b);

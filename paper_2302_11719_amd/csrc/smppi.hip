@@ -385,24 +385,47 @@ extern "C" smppi_status smppi_device_errors(smppi_ctx ctx, uint32_t* flags) {
   return SMPPI_OK;
 }
 
+// Workgroups of the pipelines that a compute unit's LDS holds at once: `lds` dynamic bytes
+// each, 384 static ones (stage_problem), in allocations of 1280.
+static int workgroups_per_cu(smppi_ctx ctx, size_t lds) {
+  return (int)((size_t)ctx->max_lds / ((lds + 384 + 1279) / 1280 * 1280));
+}
+
 // ------------------------------------------------------------------ rollout
 // Few samples run as a step pipeline (the same bits): samples per workgroup, or 0.
 // Without obstacles, 16 samples per workgroup up to two workgroups per compute unit
 // (K = 4096, T = 50: FP32 50.7 -> 22.8 us, FP64 127 -> 31.7; at 16384 it takes 30.3 /
 // 79.6 against 23.9 / 58.2 with 64); 64 samples up to four per unit in FP32 and two in
-// FP64 (K = 65536, T = 100, FP32: 98.9 -> 77.7 us; at 131072, T = 50: 76.4 against 63.6
+// FP64 (K = 65536, T = 100, FP32: 98.9 -> 77.7 us; at 131072, T = 50: 76.4 against 61.9
 // with one wave per 64 samples, FP64 at 65536: 165.9 against 128.7).  FP32 with
 // obstacles: 64 samples up to six per unit (T = 50: K = 4096 55.2 -> 29.9 us, 65536
 // 55.9 -> 45.9, 98304 74.1 -> 65.1; at 131072 it takes 82.3 against 73.4).
+// Two more limits.  All workgroups have to be resident at once, since each stages its
+// problem: with long polylines fewer fit a unit's LDS (3000 vertices, K = 65536, T = 20
+// with obstacles: 62 us in four rounds against 30).  Longer horizons pay for a second
+// round where it is short, with obstacles six workgroups where four fit from 12 steps on
+// (512 vertices, K = 98304: T = 10 22.2 against 21.7, T = 50 above) and where three fit from
+// 40 (1024 vertices, K = 98304: T = 20 36 against 35, T = 50 68 against 73), FP64 two where one
+// fits from 20 (1500 vertices, K = 32768: T = 10 35.9 against 31.7, T = 50 115 against 130).
+// And several workgroups per unit stage for longer than they save below a few steps
+// (K = 65536: T = 5 10.7 against 9.7 us, T = 10 even; K = 45000: T = 4 8.7 against 8.5,
+// T = 6 10.0 against 10.5).
 template <class R, int NOBS>
 static int rollout_pipe_samples(smppi_ctx ctx, const smppi_batch* b, const ProblemArgs<R>& p) {
-  const size_t lds = stage_lds_bytes<R>(p.poly_max, p.t_max, p.obs_max), max = (size_t)ctx->max_lds;
+  const size_t lds = stage_lds_bytes<R>(p.poly_max, p.t_max, p.obs_max);
+  const int64_t cu = ctx->n_cu, T = p.t_max;
   const int64_t n16 = (int64_t)b->n_problems * ((b->k_max + 15) / 16);
   const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + 63) / 64);
-  if (NOBS > 0) return sizeof(R) == 4 && n64 <= 6 * ctx->n_cu && lds + sizeof(ObsPipeLds) <= max ? 64 : 0;
-  if (n16 <= 2 * ctx->n_cu && lds + sizeof(typename RolloutPipe<R, 16>::Lds) <= max) return 16;
-  if (n64 <= (sizeof(R) == 4 ? 4 : 2) * ctx->n_cu && lds + sizeof(typename RolloutPipe<R, 64>::Lds) <= max) return 64;
-  return 0;
+  if (NOBS > 0) {
+    if (sizeof(R) != 4) return 0;
+    const int fit = workgroups_per_cu(ctx, lds + sizeof(ObsPipeLds));
+    if (n64 <= std::min(fit, 6) * cu) return n64 <= 4 * cu || T >= 4 ? 64 : 0;
+    return fit >= 3 && n64 <= 6 * cu && T >= (fit >= 4 ? 12 : 40) ? 64 : 0;
+  }
+  if (n16 <= std::min(workgroups_per_cu(ctx, lds + sizeof(typename RolloutPipe<R, 16>::Lds)), 2) * cu) return 16;
+  const int fit = workgroups_per_cu(ctx, lds + sizeof(typename RolloutPipe<R, 64>::Lds));
+  if (sizeof(R) == 8) return n64 <= (fit >= 1 && T >= 20 ? 2 : std::min(fit, 2)) * cu && (n64 <= cu || T >= 3) ? 64 : 0;
+  return n64 <= std::min(fit, 4) * cu && T >= (n64 > 3 * cu ? 12 : (n64 > 2 * cu ? 5 : 1)) ? 64 : 0;
 }
 
 // e0 (if not null): event stamped with the kernel's own start.
@@ -561,11 +584,16 @@ static smppi_status rollout_c8_t(smppi_ctx ctx, const smppi_batch* b, const C8Ar
   // Few samples: the step pipeline (same bits), up to six workgroups of 64 samples
   // per compute unit in FP32 and two in FP64 (K = 4096, T = 50: 51.7 -> 32.9 us,
   // FP64 121 -> 71.9; FP32 K = 98304: 69.3 -> 61.7, at 131072 70.2 against 83.5;
-  // FP64 T = 100, K = 65536: 248 against 314), from three steps on (K = 4096: T = 2
-  // 4.9 against 5.3 us, T = 3 6.0 against 5.9).
+  // FP64 T = 100, K = 65536: 248 against 314).  All workgroups have to be resident at
+  // once (a table of 8000 points, K = 65536, T = 20: 39.6 us in two rounds against 26.6),
+  // and below a few steps the staging, by fewer threads and for every 64 samples, takes
+  // longer than the pipeline saves (K = 4096: T = 2 4.9 against 5.3 us, T = 3 6.0 against
+  // 5.9; four workgroups per unit one step more, six three, 4000 points one).
   const int64_t n64 = (int64_t)b->n_problems * ((b->k_max + WAVE - 1) / WAVE);
   const size_t lds_p = lds + sizeof(C8PipeLds<R>);
-  if (a.t_max >= 3 && n64 <= (sizeof(R) == 4 ? 6 : 2) * ctx->n_cu && lds_p <= (size_t)ctx->max_lds) {
+  const int cu = ctx->n_cu, most = std::min(workgroups_per_cu(ctx, lds_p), sizeof(R) == 4 ? 6 : 2);
+  const int least_T = 3 + (n64 > 4 * cu ? 3 : (n64 > 2 * cu ? 1 : 0)) + a.n_max / 4000;
+  if (n64 <= (int64_t)most * cu && a.t_max >= least_T) {
     hipLaunchKernelGGL((k_rollout_c8_pipe<R>), dim3((b->k_max + WAVE - 1) / WAVE, b->n_problems), dim3(C8P_BLK), lds_p,
                        s, a, static_cast<R*>(S), static_cast<R*>(eps_out));
     return check_launch(ctx, "k_rollout_c8_pipe");
