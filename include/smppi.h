@@ -288,8 +288,8 @@ smppi_status smppi_update(smppi_ctx ctx, const smppi_batch* batch, const smppi_m
  * where sample m's trajectory uses the same noise as smppi_rollout.  The forward
  * pass stores every state, unclipped control and window segment in the ctx scratch
  * when that takes at most 1 GiB (B x ceil(k_max / 64) x 64 x (t_max + 1) x
- * (8 dtype bytes + 4)) and the ctx holds that much (it may have been reserved for a
- * larger batch, beyond that limit); otherwise states are recomputed from per-sample
+ * (8 dtype bytes + 4)), the ctx holds that much (it may have been reserved for a
+ * larger batch, beyond that limit) and the horizon is not very short; otherwise states are recomputed from per-sample
  * checkpoints (every min(ceil(sqrt(t_max)), 12) steps, with each step's window
  * segment).  The two agree up to rounding.  Groups of 64 samples without upstream
  * gradient are skipped.  Every 64 samples write a partial; a second small kernel

@@ -500,6 +500,18 @@ extern "C" smppi_status smppi_rollout(smppi_ctx ctx, const smppi_batch* batch, c
   return rollout_t<double>(ctx, batch, model, cost, noise, track, x0, V, iter, S, eps_out, s);
 }
 
+// Whether the adjoint's pipelines over stored states are faster than the one-wave kernels
+// from checkpoints: always with few workgroups; with several per compute unit their
+// staging and start have to be paid back over the horizon.  FP32 from two per unit on:
+// T = 1 4 to 11 % slower, T = 2 up to 8, T = 3 2 to 20 % faster (1000 problems, K = 131072,
+// both models).  FP64 from one per unit on, as fewer fit its LDS: T = 4 12 to 25 % slower
+// (1000 problems; 1000 vertices, K = 33000), T = 5 even to 40 % faster.
+template <class R>
+static bool adjoint_pipe_pays(smppi_ctx ctx, const smppi_batch* b) {
+  const int64_t groups = (int64_t)b->n_problems * ((b->k_max + WAVE - 1) / WAVE);
+  return sizeof(R) == 4 ? b->t_max >= 3 || groups <= 2 * ctx->n_cu : b->t_max >= 5 || groups <= ctx->n_cu;
+}
+
 // The per-problem validity flags at the end of the adjoint scratch.
 static uint32_t* adjoint_valid(const AdjScratch& as, void* scratch) {
   return reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(scratch) + as.part_bytes + as.slice_bytes) -
@@ -642,7 +654,7 @@ static smppi_status backward_c8_t(smppi_ctx ctx, const smppi_batch* b, const C8A
   g.valid = adjoint_valid(as, ctx->scratch);
   g.ck = static_cast<unsigned char*>(ctx->scratch) + as.ck_off;
   const size_t lds_p = c8_stage_bytes<R>(a.n_max, a.t_max) + sizeof(C8AdjPipeLds<R>);
-  if (as.stored && lds_p <= (size_t)ctx->max_lds) {
+  if (as.stored && adjoint_pipe_pays<R>(ctx, b) && lds_p <= (size_t)ctx->max_lds) {
     const C8BackwardPipeArgs<R> pa{g, g.ck};
     hipLaunchKernelGGL((k_backward_c8_pipe<R>), dim3(g.nblk_max, b->n_problems), dim3(RP_BLK), lds_p, s, pa);
     if ((st = check_launch(ctx, "k_backward_c8_pipe"))) return st;
@@ -848,7 +860,7 @@ static smppi_status launch_backward(smppi_ctx ctx, const smppi_batch* b, const B
                                     hipStream_t s) {
   const size_t lds_p =
       stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, adj_pipe_obs<R>(a.p.obs_max)) + sizeof(AdjPipeLds<R>);
-  if (stored && lds_p <= (size_t)ctx->max_lds) {
+  if (stored && adjoint_pipe_pays<R>(ctx, b) && lds_p <= (size_t)ctx->max_lds) {
     const BackwardPipeArgs<R> pa{a, a.ck};
     hipLaunchKernelGGL((k_backward_pipe<R, NOBS>), dim3(a.nblk_max, b->n_problems), dim3(RP_BLK), lds_p, s, pa);
     return check_launch(ctx, "k_backward_pipe");
