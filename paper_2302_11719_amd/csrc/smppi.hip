@@ -780,12 +780,17 @@ extern "C" smppi_status smppi_execute_curvilinear(smppi_ctx ctx, const smppi_bat
 // Threads and register slots from the largest problem: 256 threads hold up to
 // 1024 samples (fewer waves to meet in the reductions), 1024 threads up to
 // 4096, 16384 or, in FP32, 65536 (64 values and their temporaries just fit the
-// 128 registers of a 1024-thread workgroup; 64 doubles do not).
+// 128 registers of a 1024-thread workgroup; 64 doubles do not).  A second problem on
+// each compute unit waits for such a workgroup (300 problems of K = 2000: 6.8 us
+// against 5.3 with 256 threads; 3000 problems, one of K = 1100, the others of 200: 25.5
+// against 7.1), which pays up to four per unit for the largest only (600 of K = 12000:
+// 16.7 against 23.2).
 template <class R>
-static void launch_weights(const smppi_batch* b, const R* S, double lambda, R* w, R* stats, hipStream_t s) {
+static void launch_weights(smppi_ctx ctx, const smppi_batch* b, const R* S, double lambda, R* w, R* stats, hipStream_t s) {
   const dim3 grid(b->n_problems);
   const R il = (R)(1.0 / lambda);
-  if (b->k_max <= 1024)
+  const bool wide = b->n_problems <= (b->k_max > 8192 ? 4 : 1) * ctx->n_cu;
+  if (b->k_max <= 1024 || !wide)
     hipLaunchKernelGGL((k_weights<R, 256, 4, true>), grid, dim3(256), 0, s, b->k_off, S, il, w, stats);
   else if (b->k_max <= 4096)
     hipLaunchKernelGGL((k_weights<R, 1024, 4, true>), grid, dim3(1024), 0, s, b->k_off, S, il, w, stats);
@@ -808,10 +813,10 @@ extern "C" smppi_status smppi_weights(smppi_ctx ctx, const smppi_batch* batch, c
   (void)hipSetDevice(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (batch->dtype == SMPPI_F32)
-    launch_weights<float>(batch, static_cast<const float*>(S), lambda, static_cast<float*>(w),
+    launch_weights<float>(ctx, batch, static_cast<const float*>(S), lambda, static_cast<float*>(w),
                           static_cast<float*>(stats), s);
   else
-    launch_weights<double>(batch, static_cast<const double*>(S), lambda, static_cast<double*>(w),
+    launch_weights<double>(ctx, batch, static_cast<const double*>(S), lambda, static_cast<double*>(w),
                            static_cast<double*>(stats), s);
   return check_launch(ctx, "k_weights");
 }
