@@ -639,9 +639,11 @@ __global__ __launch_bounds__(UPD_BLOCK) void k_update(UpdateArgs<R> a) {
       for (int i = threadIdx.x; i < 2 * d.T; i += blockDim.x) Vpb[i] = Vb[i];
     return;
   }
+  // (no division before this: in ragged batches most workgroups leave here)
+  const int m_base = blockIdx.x * a.spw;
+  if (m_base >= d.K) return;
   const int nblk = (d.K + a.spw - 1) / a.spw;
-  if ((int)blockIdx.x >= nblk) return;
-  const int m = blockIdx.x * a.spw + threadIdx.x;
+  const int m = m_base + threadIdx.x;
   const int ms[1] = {m};
   const R ws[1] = {((int)threadIdx.x < a.spw && m < d.K) ? a.w[d.k0 + m] : R(0)};
   R* gp = a.part + ((size_t)b * a.nblk_max + blockIdx.x) * 2 * a.p.t_max;
