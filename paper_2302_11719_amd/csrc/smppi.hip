@@ -865,12 +865,19 @@ static smppi_status launch_backward(smppi_ctx ctx, const smppi_batch* b, const B
                                     hipStream_t s) {
   const size_t lds_p =
       stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, adj_pipe_obs<R>(a.p.obs_max)) + sizeof(AdjPipeLds<R>);
-  if (stored && adjoint_pipe_pays<R>(ctx, b) && lds_p <= (size_t)ctx->max_lds) {
+  const size_t lds = stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, a.p.obs_max) + adj_lds_bytes<R>(a.p.t_max, a.seg_len);
+  // Seven or eight one-wave workgroups per compute unit that are resident at once beat the
+  // FP64 pipeline's four rounds of two (2000 problems, T = 10: 127 against 152 us; K = 131072,
+  // T = 5 77 against 101, T = 16 198 against 217; seven: T = 12 153 against 157, T = 14 even;
+  // six: K = 98304, T = 5 84 against 77).
+  const int64_t groups = (int64_t)b->n_problems * a.nblk_max, cu = ctx->n_cu;
+  const bool one_round = sizeof(R) == 8 && groups > (b->t_max >= 14 ? 7 : 6) * cu &&
+                         groups <= std::min(workgroups_per_cu(ctx, lds), 8) * cu;
+  if (stored && adjoint_pipe_pays<R>(ctx, b) && !one_round && lds_p <= (size_t)ctx->max_lds) {
     const BackwardPipeArgs<R> pa{a, a.ck};
     hipLaunchKernelGGL((k_backward_pipe<R, NOBS>), dim3(a.nblk_max, b->n_problems), dim3(RP_BLK), lds_p, s, pa);
     return check_launch(ctx, "k_backward_pipe");
   }
-  const size_t lds = stage_lds_bytes<R>(a.p.poly_max, a.p.t_max, a.p.obs_max) + adj_lds_bytes<R>(a.p.t_max, a.seg_len);
   if (lds > (size_t)ctx->max_lds)
     return fail(ctx, SMPPI_ERR_SHAPE, "adjoint needs %zu B of LDS per workgroup (device max %d)", lds, ctx->max_lds);
   hipLaunchKernelGGL((k_backward<R, NOBS>), dim3(a.nblk_max, b->n_problems), dim3(WAVE), lds, s, a);

@@ -80,3 +80,24 @@ def test_adjoints_agree_with_a_problem_alone(dtype, B, Ts, tol, curvilinear):
             ref = grad([probs[b]], b)[0]
             assert np.abs(got[b] - ref).max() <= tol * np.abs(ref).max(), (T, b)
     assert ctx().device_errors() == 0
+
+
+@pytest.mark.parametrize("B,T", [(1537, 8), (2048, 5), (2048, 16), (2049, 8)])
+def test_fp64_adjoints_in_one_round_agree_with_a_problem_alone(B, T):
+    """Both sides of 7 and 8 one-wave workgroups per compute unit.  Single samples over up to
+    16 steps: some 700 chained operations, whose roundings of 1e-16 add up to 26 of them."""
+    M, C = params(F64)
+    probs = prep([_problem(1, T, n_s=32, b=b % 8) for b in range(B)], F64)
+
+    def grad(ps, pid_base):
+        db = core.DeviceBatch(ps, dtype=F64, pid_base=pid_base)
+        return db.controls(core.rollout_backward(ctx(), db, M, C, 5, torch.ones(db.sum_K, dtype=F64, device="cuda"),
+                                                 W.OBJ_TOTAL))
+
+    for b, p in enumerate(probs):
+        p.pid = b
+    got = grad(probs, 0)
+    for b in (0, 7, B - 1):
+        ref = grad([probs[b]], b)[0]
+        assert np.abs(got[b] - ref).max() <= 3e-14 * np.abs(ref).max(), b
+    assert ctx().device_errors() == 0
