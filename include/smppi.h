@@ -289,9 +289,10 @@ smppi_status smppi_update(smppi_ctx ctx, const smppi_batch* batch, const smppi_m
  * pass stores every state, unclipped control and window segment in the ctx scratch
  * when that takes at most 1 GiB (B x ceil(k_max / 64) x 64 x (t_max + 1) x
  * (8 dtype bytes + 4)), the ctx holds that much (it may have been reserved for a
- * larger batch, beyond that limit) and the horizon is not very short; otherwise states are recomputed from per-sample
- * checkpoints (every min(ceil(sqrt(t_max)), 12) steps, with each step's window
- * segment).  The two agree up to rounding.  Groups of 64 samples without upstream
+ * larger batch, beyond that limit) and it is the faster way (not at the shortest
+ * horizons, nor for some FP64 batches); otherwise states are recomputed from
+ * per-sample checkpoints (every min(ceil(sqrt(t_max)), 12) steps, with each step's
+ * window segment).  The two agree up to rounding.  Groups of 64 samples without upstream
  * gradient are skipped.  Every 64 samples write a partial; a second small kernel
  * adds them in a fixed order (the result does not depend on scheduling).  grad_V
  * has the layout of V (dtype).  Gradients pass through the clip where it is inactive and
